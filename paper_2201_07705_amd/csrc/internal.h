@@ -33,6 +33,7 @@ struct Blob {
     void *w_dev = nullptr;           // resident weights, null if streamed
     float *aff_dev = nullptr;        // scale[rows] then shift[rows], resident
     uint8_t *w_pinned = nullptr;     // pinned host copy of a streamed blob
+    bool finite = true;              // float32 conv with padding: every weight is finite
     int users = 0;                   // registered layers using this copy
     // weight cache (GEMEL_OPT_SWAP_CACHE): number in placement order, offset
     // in the cache (-1: not cached), event recorded after its last load
@@ -82,7 +83,7 @@ struct Patch {
 };
 
 enum LaunchType {
-    L_PACK, L_CONV_BF16, L_CONV_F32, L_CONV_REDUCE, L_FC_BF16, L_FC_F32, L_FC_REDUCE,
+    L_PACK, L_CONV_BF16, L_CONV_F32, L_CONV_REDUCE, L_FC_BF16, L_FC_REDUCE,
     L_MAXPOOL, L_AVGPOOL, L_UPSAMPLE, L_CONCAT, L_EXPORT
 };
 

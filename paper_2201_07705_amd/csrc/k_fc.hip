@@ -231,19 +231,6 @@ __global__ __launch_bounds__(256) void fc_bf16_kernel(const FcArgs a) {
     }
 }
 
-// float32 FC: one thread per (frame, neuron), fp32 FMA over K.
-__global__ __launch_bounds__(256) void fc_f32_kernel(const FcArgs a) {
-    const long idx = (long)blockIdx.x * 256 + threadIdx.x;
-    if (idx >= (long)a.M * a.N) return;
-    const int f = (int)(idx / a.N), n = (int)(idx - (long)f * a.N);
-    const FcSeg &sg = a.seg[fc_seg(a, f)];
-    const float *x = (const float *)sg.in + (size_t)(f - sg.f_start) * a.K;
-    const float *w = (const float *)a.w + (size_t)n * a.K;
-    float acc = 0.f;
-    for (int k = 0; k < a.K; ++k) acc = fmaf(x[k], w[k], acc);
-    fc_store(a, f, n, acc, false);
-}
-
 template <bool BF16>
 __global__ __launch_bounds__(256) void fc_reduce_kernel(const FcArgs a) {
     const long idx = (long)blockIdx.x * 256 + threadIdx.x;
@@ -297,12 +284,6 @@ hipError_t launch_fc_bf16(const FcArgs &a, const Sink &sk) {
                         reinterpret_cast<const void *>(&fc_bf16_kernel<4>)};
     const void *fn = t[mb - 1];
     return submit(sk, fn, grid, block, a);
-}
-
-hipError_t launch_fc_f32(const FcArgs &a, const Sink &sk) {
-    if (!fc_args_ok(a) || a.k_splits != 1 || a.grouped) return hipErrorInvalidValue;
-    const long n = (long)a.M * a.N;
-    return submit(sk, reinterpret_cast<const void *>(&fc_f32_kernel), dim3((unsigned)((n + 255) / 256)), dim3(256), a);
 }
 
 hipError_t launch_fc_reduce(const FcArgs &a, bool bf16, const Sink &sk) {

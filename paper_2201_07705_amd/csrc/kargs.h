@@ -78,7 +78,9 @@ struct ConvArgs {
                           // pool)
     const void *pf;       // or null: bytes [0, pf_bytes) read (into the
     uint32_t pf_bytes;    // caches) once the tiles are done, the weights of
-    int32_t pf_pad;       // the conv that follows on the stream
+                          // the conv that follows on the stream
+    int32_t direct;       // float32: skip taps outside the image instead of
+                          // multiplying zeros with their weights
     ConvSeg seg[GEMEL_MAX_SEG];
 };
 

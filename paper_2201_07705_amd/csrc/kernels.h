@@ -111,7 +111,10 @@ inline int tile_dma_depth(int tile) {
 constexpr int STEM_MAX_TAPS = 52;
 bool conv_stem_supported(const ConvArgs &a);
 hipError_t launch_conv_stem(const ConvArgs &a, const Sink &sk);
+// float32 conv: the matrix-core kernel (k_conv_f32.hip), or with a.direct
+// the scalar one.
 hipError_t launch_conv_f32(const ConvArgs &a, const Sink &sk);
+hipError_t launch_conv_f32_mfma(const ConvArgs &a, const Sink &sk);
 // Split-K reduction + fused epilogue (bf16 or f32 internal activations).
 hipError_t launch_conv_reduce(const ReduceArgs &a, bool bf16, const Sink &sk);
 
@@ -123,7 +126,6 @@ hipError_t static_scratch(int device, void **ptr);
 hipError_t launch_fill_u32(uint32_t *p, size_t n, uint32_t v, const Sink &sk);
 
 hipError_t launch_fc_bf16(const FcArgs &a, const Sink &sk);
-hipError_t launch_fc_f32(const FcArgs &a, const Sink &sk);
 hipError_t launch_fc_reduce(const FcArgs &a, bool bf16, const Sink &sk);
 
 // Input pack: caller NCHW f32 -> NHWC physical channels (bf16 or f32).

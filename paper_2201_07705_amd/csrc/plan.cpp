@@ -1231,7 +1231,6 @@ static gemel_status build_plan(gemel_ctx *ctx, const std::vector<int> &ids, cons
             for (auto [s, l] : nd.mem) M += (int64_t)nfr[(size_t)s] * layer(s, l).out_h * layer(s, l).out_w;
             const bool direct = direct_output(L0);
             const bool fc_small = L0.op == GEMEL_OP_FC && bf16 && M <= 64;
-            const bool fc_f32 = L0.op == GEMEL_OP_FC && !bf16;
             // weight chunks: a resident blob is one chunk with no copy
             std::vector<std::pair<int64_t, int64_t>> rows;  // (row0, nrows)
             if (blob->w_dev || ctx->cache_mode) {   // resident, or cached when the round runs
@@ -1271,7 +1270,7 @@ static gemel_status build_plan(gemel_ctx *ctx, const std::vector<int> &ids, cons
                     P.streamed_bytes += P.chunks.back().bytes();
                 }
                 const void *wptr = blob->w_dev ? (const void *)((const char *)blob->w_dev) : nullptr;
-                if (fc_small || fc_f32) {
+                if (fc_small) {
                     FcArgs &a = Lc.fc;
                     a.w = wptr;
                     a.M = (int)M; a.N = (int)nrows; a.K = (int)blob->k;
@@ -1301,21 +1300,15 @@ static gemel_status build_plan(gemel_ctx *ctx, const std::vector<int> &ids, cons
                     }
                     Lc.kind = GEMEL_K_FC;
                     a.grouped = grouped ? 1 : 0;
-                    if (fc_f32) {
-                        a.k_splits = 1;
-                        a.k_per_split = a.K;
-                        Lc.type = L_FC_F32;
-                    } else {
-                        pick_fc_config(slice_frames, a.N, a.K, a.k_splits, a.k_per_split);
-                        Lc.type = L_FC_BF16;
-                        if (a.k_splits > 1) {
-                            step_partial[(size_t)step] = std::max(step_partial[(size_t)step], (size_t)a.k_splits * a.M * a.N * 4);
-                            if (ctx->opt.splitk_fused)
-                                Lc.ctr_n = (a.N + 63) / 64 * (grouped ? a.nseg : 1);
-                        }
+                    pick_fc_config(slice_frames, a.N, a.K, a.k_splits, a.k_per_split);
+                    Lc.type = L_FC_BF16;
+                    if (a.k_splits > 1) {
+                        step_partial[(size_t)step] = std::max(step_partial[(size_t)step], (size_t)a.k_splits * a.M * a.N * 4);
+                        if (ctx->opt.splitk_fused)
+                            Lc.ctr_n = (a.N + 63) / 64 * (grouped ? a.nseg : 1);
                     }
                     P.launches.push_back(Lc);
-                    if (Lc.type == L_FC_BF16 && a.k_splits > 1 && !Lc.ctr_n) {
+                    if (a.k_splits > 1 && !Lc.ctr_n) {
                         Launch R = Lc;
                         R.type = L_FC_REDUCE;
                         R.kind = GEMEL_K_SPLITK_REDUCE;
@@ -1334,7 +1327,7 @@ static gemel_status build_plan(gemel_ctx *ctx, const std::vector<int> &ids, cons
                     a.H = L0.in_h; a.W = L0.in_w; a.Cin = L0.in_phys; a.in_cs = L0.in_phys;
                     a.Ho = L0.out_h; a.Wo = L0.out_w;
                     a.kh = L0.kh; a.kw = L0.kw; a.stride = L0.stride; a.pad = L0.pad;
-                } else {  // FC over many frames: a 1x1 conv on a 1x1 map with Cin = K
+                } else {  // FC over many frames, or float32: a 1x1 conv on a 1x1 map with Cin = K
                     a.H = a.W = 1; a.Cin = a.in_cs = (int)blob->k;
                     a.Ho = a.Wo = 1;
                     a.kh = a.kw = 1; a.stride = 1; a.pad = 0;
@@ -1411,6 +1404,7 @@ static gemel_status build_plan(gemel_ctx *ctx, const std::vector<int> &ids, cons
                 } else {
                     a.k_splits = 1;
                     a.k_per_split = a.K;
+                    a.direct = !blob->finite;
                     Lc.type = L_CONV_F32;
                     Lc.kind = L0.op == GEMEL_OP_CONV ? GEMEL_K_CONV_F32 : GEMEL_K_FC;
                 }
@@ -1488,12 +1482,12 @@ static gemel_status build_plan(gemel_ctx *ctx, const std::vector<int> &ids, cons
         tag_launches(first_launch, NN + (int)e);
     }
     if (const char *tr = std::getenv("GEMEL_TRACE_PLAN"); tr && tr[0] == '1') {
-        static const char *names[] = {"pack", "conv_bf16", "conv_f32", "conv_reduce", "fc_bf16", "fc_f32",
+        static const char *names[] = {"pack", "conv_bf16", "conv_f32", "conv_reduce", "fc_bf16",
                                       "fc_reduce", "maxpool", "avgpool", "upsample", "concat", "export"};
         for (size_t i = 0; i < P.launches.size(); ++i) {
             const Launch &L = P.launches[i];
             const bool cv = L.type == L_CONV_BF16 || L.type == L_CONV_F32;
-            const bool fcl = L.type == L_FC_BF16 || L.type == L_FC_F32;
+            const bool fcl = L.type == L_FC_BF16;
             std::fprintf(stderr, "plan %zu %s M=%d N=%d K=%d tile=%d splits=%d segs=%d gflop=%.3f mb=%.2f st=%d\n", i,
                          names[L.type], cv ? L.conv.M : fcl ? L.fc.M : 0, cv ? L.conv.N : fcl ? L.fc.N : 0,
                          cv ? L.conv.K : fcl ? L.fc.K : 0, L.tile,
@@ -1661,7 +1655,6 @@ hipError_t launch_one(Launch &L, const CallPtrs &cp, const Plan &P, void *wptr, 
             case L_CONV_F32: L.conv.seg[p.seg].out = o; break;
             case L_CONV_REDUCE: L.red.seg[p.seg].out = o; break;
             case L_FC_BF16:
-            case L_FC_F32:
             case L_FC_REDUCE: L.fc.seg[p.seg].out = o; break;
             default: L.ew.seg[p.seg].out = o; break;
             }
@@ -1677,7 +1670,6 @@ hipError_t launch_one(Launch &L, const CallPtrs &cp, const Plan &P, void *wptr, 
     case L_CONV_F32: return launch_conv_f32(L.conv, st);
     case L_CONV_REDUCE: return launch_conv_reduce(L.red, L.bf16, st);
     case L_FC_BF16: return launch_fc_bf16(L.fc, st);
-    case L_FC_F32: return launch_fc_f32(L.fc, st);
     case L_FC_REDUCE: return launch_fc_reduce(L.fc, L.bf16, st);
     case L_MAXPOOL: return launch_maxpool(L.ew, L.bf16, st);
     case L_AVGPOOL: return launch_avgpool(L.ew, L.bf16, st);

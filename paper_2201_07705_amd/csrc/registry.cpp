@@ -90,6 +90,10 @@ static std::shared_ptr<Blob> make_blob(const gemel_layer_desc &d, const Layer &l
                 for (int64_t p = 0; p < hw; ++p)
                     put(o, p * l.in_cp + c, d.weight[(int64_t)o * l.cin + c * hw + p]);
     }
+    if (b->elem == 4 && l.op == GEMEL_OP_CONV && l.pad > 0) {
+        const float *w = (const float *)b->w.data();
+        for (int64_t i = 0; i < b->rows * b->k; ++i) b->finite &= std::isfinite(w[i]);
+    }
     b->scale.assign((size_t)b->rows, 0.f);
     b->shift.assign((size_t)b->rows, 0.f);
     for (int o = 0; o < l.cout; ++o) {
