@@ -43,88 +43,218 @@ __device__ __forceinline__ void copy8(float *d, const float *s) {
     *(float4 *)(d + 4) = *(const float4 *)(s + 4);
 }
 
-// Caller frames NCHW f32 -> NHWC, channels zero-padded to Co.
-template <typename T>
-__global__ __launch_bounds__(256) void pack_kernel(const EwArgs a) {
+// Caller frames NCHW f32 -> NHWC, channels zero-padded to Co, for images
+// (Co = 8): bound by HBM latency and bytes (12 or 16 read for 16 or 32
+// written a pixel), so a thread has the loads of PX pixels in flight, 256
+// apart, and every store instruction writes whole lines. CL: the channel
+// count, or 8 for any (up to 8, those beyond it read again and dropped). The
+// loads are unconditional, at clamped addresses: a load inside a branch is
+// waited for at the branch's end.
+// Grid: x = frames * ceil(hw / (256 * PX)), y = segment.
+template <typename T, int PX, int CL>
+__global__ __launch_bounds__(256) void pack_image_kernel(const EwArgs a) {
     const EwSeg &sg = a.seg[blockIdx.y];
-    const long hw = (long)a.H * a.W;
-    const long idx = (long)blockIdx.x * 256 + threadIdx.x;
-    if (idx >= sg.frames * hw) return;
-    const long f = idx / hw, p = idx - f * hw;
-    const float *src = (const float *)sg.in0 + f * a.c_logical * hw + p;
-    T *dst = (T *)sg.out + idx * a.Co;
-    for (int c0 = 0; c0 < a.Co; c0 += 8) {
-        float v[8];
+    const int hw = a.H * a.W, per = (hw + 256 * PX - 1) / (256 * PX);
+    const int f = (int)blockIdx.x / per, p0 = ((int)blockIdx.x - f * per) * 256 * PX + (int)threadIdx.x;
+    if (f >= sg.frames) return;
+    const float *src = (const float *)sg.in0 + (size_t)f * a.c_logical * hw;
+    T *dst = (T *)sg.out + (size_t)f * hw * 8;
+    float v[PX][8];
 #pragma unroll
-        for (int j = 0; j < 8; ++j) v[j] = (c0 + j < a.c_logical) ? src[(c0 + j) * hw] : 0.f;
-        store8(dst + c0, v);
+    for (int q = 0; q < PX; ++q) {
+        const int p = min(p0 + q * 256, hw - 1);
+#pragma unroll
+        for (int j = 0; j < CL; ++j) v[q][j] = src[(size_t)(CL == 8 ? min(j, a.c_logical - 1) : j) * hw + p];
+    }
+#pragma unroll
+    for (int q = 0; q < PX; ++q) {
+        const int p = p0 + q * 256;
+#pragma unroll
+        for (int j = 0; j < 8; ++j) v[q][j] = j < CL && j < a.c_logical ? v[q][j] : 0.f;
+        if (p < hw) store8(dst + (size_t)p * 8, v[q]);
     }
 }
 
-// Max pool, window k, stride, pad; out-of-range taps are skipped (= -inf).
+// 16-byte chunks of a 64-pixel x 64-channel tile in LDS, the chunk position
+// swizzled by the pixel: both one chunk of consecutive pixels and the
+// consecutive chunks of one pixel then fall on distinct banks.
 template <typename T>
+struct TransTile {
+    static constexpr int EPC = 16 / (int)sizeof(T);   // elements per chunk
+    static constexpr int CH = 64 / EPC;                // chunks per pixel
+    static constexpr int CPW = CH / 4;                 // chunks per wave
+    static constexpr int RPI = 256 / CH;               // pixels the workgroup covers per row pass
+    static __device__ __forceinline__ int slot(int px, int ch) { return px * CH + (ch ^ (px & (CH - 1))); }
+    static __device__ __forceinline__ uint4 chunk(const float *v) {
+        if constexpr (sizeof(T) == 2) {
+            auto two = [&](int j) { return (uint32_t)m_f2bf(v[j]) | ((uint32_t)m_f2bf(v[j + 1]) << 16); };
+            return make_uint4(two(0), two(2), two(4), two(6));
+        } else {
+            return make_uint4(__float_as_uint(v[0]), __float_as_uint(v[1]), __float_as_uint(v[2]), __float_as_uint(v[3]));
+        }
+    }
+    static __device__ __forceinline__ float elem(const uint4 &x, int j) {
+        const uint32_t w[4] = {x.x, x.y, x.z, x.w};
+        if constexpr (sizeof(T) == 2)
+            return __uint_as_float((j & 1) ? (w[j >> 1] & 0xffff0000u) : (w[j >> 1] << 16));
+        else
+            return __uint_as_float(w[j]);
+    }
+};
+
+// The same for more than 8 channels: a 64-pixel x 64-channel tile turned in
+// LDS. Reads are 256 bytes of one channel plane per wave, 16 in flight per
+// thread; writes are 64 channels of a pixel (128 bytes of bf16). One thread
+// per pixel walking all channels (the form before) left the chip idle: 8
+// frames of 1024 x 14 x 14 took 286 us on 8 workgroups, 4.4 us here; 16
+// frames of 256 x 56 x 56 72 us, 14 us here (5.5 TB/s).
+// Grid: x = frames * ceil(hw / 64) * ceil(Co / 64), y = segment.
+template <typename T>
+__global__ __launch_bounds__(256) void pack_tile_kernel(const EwArgs a) {
+    using TT = TransTile<T>;
+    __shared__ uint4 lds[64 * TT::CH];
+    const EwSeg &sg = a.seg[blockIdx.y];
+    const int hw = a.H * a.W, per = (hw + 63) / 64, cb = (a.Co + 63) / 64;
+    const int tile = (int)blockIdx.x / cb, c0 = ((int)blockIdx.x - tile * cb) * 64;
+    const int f = tile / per, p0 = (tile - f * per) * 64;
+    if (f >= sg.frames) return;   // uniform: before the barrier
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const float *src = (const float *)sg.in0 + (size_t)f * a.c_logical * hw + min(p0 + lane, hw - 1);
+    float v[16];
+#pragma unroll
+    for (int j = 0; j < 16; ++j) v[j] = src[(size_t)min(c0 + wave * 16 + j, a.c_logical - 1) * hw];
+#pragma unroll
+    for (int j = 0; j < 16; ++j) v[j] = c0 + wave * 16 + j < a.c_logical ? v[j] : 0.f;
+#pragma unroll
+    for (int q = 0; q < TT::CPW; ++q) {
+        lds[TT::slot(lane, wave * TT::CPW + q)] = TT::chunk(v + q * TT::EPC);
+    }
+    __syncthreads();
+    const int ch = threadIdx.x % TT::CH;
+    if (c0 + ch * TT::EPC >= a.Co) return;
+    T *dst = (T *)sg.out + ((size_t)f * hw + p0) * a.Co + c0 + ch * TT::EPC;
+#pragma unroll
+    for (int q = 0; q < 64 / TT::RPI; ++q) {
+        const int px = threadIdx.x / TT::CH + q * TT::RPI;
+        if (p0 + px < hw) *(uint4 *)(dst + (size_t)px * a.Co) = lds[TT::slot(px, ch)];
+    }
+}
+
+// Grid of ceil(items / 256) workgroups per frame: this thread's frame and
+// its item of the frame (32-bit divisions, the frame's by scalars). False
+// for threads beyond either.
+__device__ __forceinline__ bool frame_item(uint32_t items, int frames, uint32_t &f, uint32_t &idx) {
+    const uint32_t per = (items + 255) / 256;
+    f = blockIdx.x / per;
+    idx = (blockIdx.x - f * per) * 256 + threadIdx.x;
+    return (int)f < frames && idx < items;
+}
+
+// Max pool, window k, stride, pad: out-of-range taps are skipped (= -inf).
+// K > 0: the window size at compile time; taps beyond the border read the
+// nearest pixel of the window instead (its maximum is the same), so that
+// all K * K loads are in flight at once (8 frames of 64 x 112 x 112, 3x3
+// stride 2: 7.3 -> 5.4 us).
+template <typename T, int K>
 __global__ __launch_bounds__(256) void maxpool_kernel(const EwArgs a) {
     const EwSeg &sg = a.seg[blockIdx.y];
-    const int ch = a.C / 8;
-    const long idx = (long)blockIdx.x * 256 + threadIdx.x;
-    if (idx >= (long)sg.frames * a.Ho * a.Wo * ch) return;
-    const int cc = (int)(idx % ch);
-    long t = idx / ch;
-    const int wo = (int)(t % a.Wo);
-    t /= a.Wo;
-    const int ho = (int)(t % a.Ho);
-    const long f = t / a.Ho;
-    const T *in = (const T *)sg.in0 + f * a.H * a.W * a.C + cc * 8;
+    const uint32_t ch = (uint32_t)a.C / 8, items = (uint32_t)a.Ho * a.Wo * ch;
+    uint32_t f, idx;
+    if (!frame_item(items, sg.frames, f, idx)) return;
+    const uint32_t px = idx / ch, row = px / (uint32_t)a.Wo;
+    const int cc = (int)(idx - px * ch), wo = (int)(px - row * a.Wo), ho = (int)row;
+    const T *in = (const T *)sg.in0 + (size_t)f * a.H * a.W * a.C + cc * 8;
+    const int h0 = ho * a.stride - a.pad, w0 = wo * a.stride - a.pad;
     float m[8];
 #pragma unroll
     for (int j = 0; j < 8; ++j) m[j] = -INFINITY;
-    for (int i = 0; i < a.k; ++i) {
-        const int hi = ho * a.stride - a.pad + i;
-        if (hi < 0 || hi >= a.H) continue;
-        for (int q = 0; q < a.k; ++q) {
-            const int wi = wo * a.stride - a.pad + q;
-            if (wi < 0 || wi >= a.W) continue;
-            float v[8];
-            load8(in + ((long)hi * a.W + wi) * a.C, v);
+    if constexpr (K > 0) {
+        const T *p[K];
+        int wi[K];
 #pragma unroll
-            for (int j = 0; j < 8; ++j) m[j] = fmaxf(m[j], v[j]);
+        for (int i = 0; i < K; ++i) {
+            p[i] = in + (size_t)min(max(h0 + i, 0), a.H - 1) * a.W * a.C;
+            wi[i] = min(max(w0 + i, 0), a.W - 1) * a.C;
+        }
+#pragma unroll
+        for (int i = 0; i < K; ++i)
+#pragma unroll
+            for (int q = 0; q < K; ++q) {
+                float v[8];
+                load8(p[i] + wi[q], v);
+#pragma unroll
+                for (int j = 0; j < 8; ++j) m[j] = fmaxf(m[j], v[j]);
+            }
+    } else {
+        for (int i = 0; i < a.k; ++i) {
+            const int hi = h0 + i;
+            if (hi < 0 || hi >= a.H) continue;
+            for (int q = 0; q < a.k; ++q) {
+                const int wi = w0 + q;
+                if (wi < 0 || wi >= a.W) continue;
+                float v[8];
+                load8(in + ((size_t)hi * a.W + wi) * a.C, v);
+#pragma unroll
+                for (int j = 0; j < 8; ++j) m[j] = fmaxf(m[j], v[j]);
+            }
         }
     }
-    store8((T *)sg.out + idx * 8, m);
+    store8((T *)sg.out + ((size_t)f * items + idx) * 8, m);
 }
 
-// Global average pool: [f][H][W][C] -> [f][C], fp32 sums. A workgroup
-// covers one frame and 64 8-channel chunks; its 4 waves take every 4th
-// pixel (independent loads in flight), and the 4 partial sums meet in LDS.
-// Grid: x = frames * ceil(chunks / 64), y = segment.
-template <typename T>
+// Global average pool: [f][H][W][C] -> [f][C], fp32 sums. Bound by the
+// latency of a thread's serial loads, so a workgroup takes CW = 4 or 16
+// 8-channel chunks of one frame and 256 / CW pixel groups, whose partial
+// sums meet in LDS (with 64 chunks and 4 groups, 16 x 16 x 32 float32 took
+// 17 us on one wave's lanes, 8 frames of 7 x 7 x 2048 bf16 6.9 us; here 2.6
+// and 4.7 us).
+// Grid: x = frames * ceil(chunks / CW), y = segment.
+template <typename T, int CW>
 __global__ __launch_bounds__(256) void avgpool_kernel(const EwArgs a) {
-    __shared__ float part[4][64][9];
+    constexpr int PG = 256 / CW;
+    __shared__ float part[PG][CW * 8 + 4];
     const EwSeg &sg = a.seg[blockIdx.y];
-    const int ch = a.C / 8, cblocks = (ch + 63) / 64;
-    const long f = blockIdx.x / cblocks;
+    const int ch = a.C / 8, cblocks = (ch + CW - 1) / CW;
+    const int f = (int)blockIdx.x / cblocks;
     if (f >= sg.frames) return;
-    const int lane = threadIdx.x & 63, pg = threadIdx.x >> 6;
-    const int cc = (int)(blockIdx.x - f * cblocks) * 64 + lane;
-    const long hw = (long)a.H * a.W;
+    const int cl = threadIdx.x % CW, pg = threadIdx.x / CW;
+    const int c0 = ((int)blockIdx.x - f * cblocks) * CW, cc = c0 + cl;
+    const int hw = a.H * a.W;
     float s[8] = {0, 0, 0, 0, 0, 0, 0, 0};
     if (cc < ch) {
-        const T *in = (const T *)sg.in0 + f * hw * a.C + cc * 8;
-        for (long p = pg; p < hw; p += 4) {
+        const T *in = (const T *)sg.in0 + (size_t)f * hw * a.C + cc * 8;
+        int p = pg;
+        for (; p + 3 * PG < hw; p += 4 * PG) {
+            float v[4][8];
+#pragma unroll
+            for (int q = 0; q < 4; ++q) load8(in + (size_t)(p + q * PG) * a.C, v[q]);
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+#pragma unroll
+                for (int j = 0; j < 8; ++j) s[j] += v[q][j];
+        }
+        for (; p < hw; p += PG) {
             float v[8];
-            load8(in + p * a.C, v);
+            load8(in + (size_t)p * a.C, v);
 #pragma unroll
             for (int j = 0; j < 8; ++j) s[j] += v[j];
         }
     }
 #pragma unroll
-    for (int j = 0; j < 8; ++j) part[pg][lane][j] = s[j];
+    for (int j = 0; j < 8; ++j) part[pg][cl * 8 + j] = s[j];
     __syncthreads();
-    if (pg == 0 && cc < ch) {
-        const float inv = 1.0f / (float)hw;
-#pragma unroll
-        for (int j = 0; j < 8; ++j) s[j] = (part[0][lane][j] + part[1][lane][j] + part[2][lane][j] + part[3][lane][j]) * inv;
-        store8((T *)sg.out + f * a.C + cc * 8, s);
+    // one thread per channel sums the groups, in order
+    const int c = threadIdx.x;
+    if (c < CW * 8 && c0 * 8 + c < a.C) {
+        float t = 0.f;
+#pragma unroll 16
+        for (int q = 0; q < PG; ++q) t += part[q][c];
+        t *= 1.0f / (float)hw;
+        T *o = (T *)sg.out + (size_t)f * a.C + c0 * 8 + c;
+        if constexpr (sizeof(T) == 2)
+            *o = m_f2bf(t);
+        else
+            *o = t;
     }
 }
 
@@ -132,54 +262,65 @@ __global__ __launch_bounds__(256) void avgpool_kernel(const EwArgs a) {
 template <typename T>
 __global__ __launch_bounds__(256) void upsample2x_kernel(const EwArgs a) {
     const EwSeg &sg = a.seg[blockIdx.y];
-    const int ch = a.C / 8;
-    const long idx = (long)blockIdx.x * 256 + threadIdx.x;
-    if (idx >= (long)sg.frames * a.Ho * a.Wo * ch) return;
-    const int cc = (int)(idx % ch);
-    long t = idx / ch;
-    const int wo = (int)(t % a.Wo);
-    t /= a.Wo;
-    const int ho = (int)(t % a.Ho);
-    const long f = t / a.Ho;
-    const T *in = (const T *)sg.in0 + ((f * a.H + ho / 2) * a.W + wo / 2) * a.C + cc * 8;
-    copy8((T *)sg.out + idx * 8, in);
+    const uint32_t ch = (uint32_t)a.C / 8, items = (uint32_t)a.Ho * a.Wo * ch;
+    uint32_t f, idx;
+    if (!frame_item(items, sg.frames, f, idx)) return;
+    const uint32_t px = idx / ch, ho = px / (uint32_t)a.Wo;
+    const uint32_t cc = idx - px * ch, wo = px - ho * a.Wo;
+    const T *in = (const T *)sg.in0 + (((size_t)f * a.H + ho / 2) * a.W + wo / 2) * a.C + cc * 8;
+    copy8((T *)sg.out + ((size_t)f * items + idx) * 8, in);
 }
 
 // Channel concat [in0 (C), in1 (C1)] -> out (C + C1), same H x W.
 template <typename T>
 __global__ __launch_bounds__(256) void concat_kernel(const EwArgs a) {
     const EwSeg &sg = a.seg[blockIdx.y];
-    const int ch = a.Co / 8;
-    const long idx = (long)blockIdx.x * 256 + threadIdx.x;
-    if (idx >= (long)sg.frames * a.H * a.W * ch) return;
-    const int cc = (int)(idx % ch);
-    const long p = idx / ch;
-    const int c = cc * 8;
+    const uint32_t ch = (uint32_t)a.Co / 8, hw = (uint32_t)a.H * a.W, items = hw * ch;
+    uint32_t f, idx;
+    if (!frame_item(items, sg.frames, f, idx)) return;
+    const uint32_t px = idx / ch;
+    const int c = (int)(idx - px * ch) * 8;
+    const size_t p = (size_t)f * hw + px;
     const T *src = c < a.C ? (const T *)sg.in0 + p * a.C + c : (const T *)sg.in1 + p * a.C1 + (c - a.C);
-    copy8((T *)sg.out + idx * 8, src);
+    copy8((T *)sg.out + ((size_t)f * items + idx) * 8, src);
 }
 
-// Internal NHWC (C physical) -> caller NCHW f32 with c_logical channels.
-// One thread per (frame, 8-channel chunk, pixel), pixels fastest: a 16-byte
-// load of the pixel's 8 channels, then 8 plane writes that consecutive
-// threads make to consecutive addresses.
+// Internal NHWC (C physical) -> caller NCHW f32 with c_logical channels: the
+// pack tile's transpose the other way round. Reads are 64 channels of a
+// pixel, writes 256 bytes of one channel plane per wave (8 x 64 x 56 x 56
+// from bf16: 5.0 us; a thread per pixel and 8 channels, reading 16 bytes of
+// each line, 6.1 us).
+// Grid: x = frames * ceil(hw / 64) * ceil(c_logical / 64), y = segment.
 template <typename T>
 __global__ __launch_bounds__(256) void export_kernel(const EwArgs a) {
+    using TT = TransTile<T>;
+    __shared__ uint4 lds[64 * TT::CH];
     const EwSeg &sg = a.seg[blockIdx.y];
-    const long hw = (long)a.H * a.W;
-    const int ch = (a.c_logical + 7) / 8;
-    const long idx = (long)blockIdx.x * 256 + threadIdx.x;
-    if (idx >= (long)sg.frames * ch * hw) return;
-    const long p = idx % hw;
-    const long t = idx / hw;
-    const int cc = (int)(t % ch);
-    const long f = t / ch;
-    float v[8];
-    load8((const T *)sg.in0 + (f * hw + p) * a.C + cc * 8, v);
-    float *o = (float *)sg.out + (f * a.c_logical + cc * 8) * hw + p;
+    const int hw = a.H * a.W, per = (hw + 63) / 64, cb = (a.c_logical + 63) / 64;
+    const int tile = (int)blockIdx.x / cb, c0 = ((int)blockIdx.x - tile * cb) * 64;
+    const int f = tile / per, p0 = (tile - f * per) * 64;
+    if (f >= sg.frames) return;   // uniform: before the barrier
+    const int ch = threadIdx.x % TT::CH, px0 = threadIdx.x / TT::CH;
+    const T *src = (const T *)sg.in0 + ((size_t)f * hw + p0) * a.C + min(c0 + ch * TT::EPC, a.C - TT::EPC);
+    uint4 x[64 / TT::RPI];
 #pragma unroll
-    for (int j = 0; j < 8; ++j)
-        if (cc * 8 + j < a.c_logical) o[j * hw] = v[j];
+    for (int q = 0; q < 64 / TT::RPI; ++q) x[q] = *(const uint4 *)(src + (size_t)min(px0 + q * TT::RPI, hw - 1 - p0) * a.C);
+#pragma unroll
+    for (int q = 0; q < 64 / TT::RPI; ++q) lds[TT::slot(px0 + q * TT::RPI, ch)] = x[q];
+    __syncthreads();
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    if (p0 + lane >= hw) return;
+    float *o = (float *)sg.out + (size_t)f * a.c_logical * hw + p0 + lane;
+#pragma unroll
+    for (int q = 0; q < TT::CPW; ++q) {
+        const int cq = wave * TT::CPW + q;
+        const uint4 v = lds[TT::slot(lane, cq)];
+#pragma unroll
+        for (int j = 0; j < TT::EPC; ++j) {
+            const int c = c0 + cq * TT::EPC + j;
+            if (c < a.c_logical) o[(size_t)c * hw] = TT::elem(v, j);
+        }
+    }
 }
 
 // A launcher with nothing to launch (no frames): the sink's timing events,
@@ -203,54 +344,88 @@ static bool ew_ok(const EwArgs &a, bool need_in1) {
     return true;
 }
 
-static hipError_t ew_launch(const void *kern, long items_per_frame, const EwArgs &a, const Sink &sk) {
-    const long items = items_per_frame * a.max_frames;
-    if (items <= 0) return submit_nothing(sk);
-    const long blocks = (items + 255) / 256;
-    if (blocks > 0x7fffffffL) return hipErrorInvalidValue;
-    return submit(sk, kern, dim3((unsigned)blocks, (unsigned)a.nseg), dim3(256), a);
+// A grid of `blocks` workgroups per frame in x, one segment in y.
+static hipError_t frame_launch(const void *kern, long blocks, const EwArgs &a, const Sink &sk) {
+    const long n = blocks * a.max_frames;
+    if (n <= 0) return submit_nothing(sk);
+    if (n > 0x7fffffffL) return hipErrorInvalidValue;
+    return submit(sk, kern, dim3((unsigned)n, (unsigned)a.nseg), dim3(256), a);
+}
+// One thread per item of a frame (frame_item).
+static hipError_t item_launch(const void *kern, long items, const EwArgs &a, const Sink &sk) {
+    return items > 0x7fffff00L ? hipErrorInvalidValue : frame_launch(kern, (items + 255) / 256, a, sk);
+}
+
+template <typename T, int PX>
+static const void *pack_image_of(int c) {
+    return c == 3   ? reinterpret_cast<const void *>(&pack_image_kernel<T, PX, 3>)
+           : c == 1 ? reinterpret_cast<const void *>(&pack_image_kernel<T, PX, 1>)
+                    : reinterpret_cast<const void *>(&pack_image_kernel<T, PX, 8>);
 }
 
 hipError_t launch_pack(const EwArgs &a, bool bf16, const Sink &sk) {
     if (!ew_ok(a, false) || a.Co % 8 || a.c_logical > a.Co || a.c_logical <= 0) return hipErrorInvalidValue;
-    const long per = (long)a.H * a.W;
-    return bf16 ? ew_launch(reinterpret_cast<const void *>(&pack_kernel<u16>), per, a, sk) : ew_launch(reinterpret_cast<const void *>(&pack_kernel<float>), per, a, sk);
+    const long hw = (long)a.H * a.W;
+    if (hw > 0x3fffffffL) return hipErrorInvalidValue;
+    if (a.Co == 8) {
+        // 4 pixels a thread where that still leaves four workgroups per CU
+        const bool wide = (hw + 1023) / 1024 * a.max_frames * a.nseg >= 1024;
+        const long px = wide ? 1024 : 256;
+        const void *k = bf16 ? (wide ? pack_image_of<u16, 4>(a.c_logical) : pack_image_of<u16, 1>(a.c_logical))
+                             : (wide ? pack_image_of<float, 4>(a.c_logical) : pack_image_of<float, 1>(a.c_logical));
+        return frame_launch(k, (hw + px - 1) / px, a, sk);
+    }
+    const void *k = bf16 ? reinterpret_cast<const void *>(&pack_tile_kernel<u16>)
+                         : reinterpret_cast<const void *>(&pack_tile_kernel<float>);
+    return frame_launch(k, (hw + 63) / 64 * ((a.Co + 63) / 64), a, sk);
+}
+
+template <typename T>
+static const void *maxpool_of(int k) {
+    return k == 2   ? reinterpret_cast<const void *>(&maxpool_kernel<T, 2>)
+           : k == 3 ? reinterpret_cast<const void *>(&maxpool_kernel<T, 3>)
+                    : reinterpret_cast<const void *>(&maxpool_kernel<T, 0>);
 }
 
 hipError_t launch_maxpool(const EwArgs &a, bool bf16, const Sink &sk) {
+    // pad < k: every window holds a pixel (what the clamped taps rely on)
     if (!ew_ok(a, false) || a.C % 8 || a.k <= 0 || a.stride <= 0 || a.pad >= a.k) return hipErrorInvalidValue;
     if (a.Ho != (a.H + 2 * a.pad - a.k) / a.stride + 1 || a.Wo != (a.W + 2 * a.pad - a.k) / a.stride + 1)
         return hipErrorInvalidValue;
-    const long per = (long)a.Ho * a.Wo * (a.C / 8);
-    return bf16 ? ew_launch(reinterpret_cast<const void *>(&maxpool_kernel<u16>), per, a, sk) : ew_launch(reinterpret_cast<const void *>(&maxpool_kernel<float>), per, a, sk);
+    return item_launch(bf16 ? maxpool_of<u16>(a.k) : maxpool_of<float>(a.k), (long)a.Ho * a.Wo * (a.C / 8), a, sk);
 }
 
 hipError_t launch_avgpool(const EwArgs &a, bool bf16, const Sink &sk) {
-    if (!ew_ok(a, false) || a.C % 8 || a.H <= 0 || a.W <= 0) return hipErrorInvalidValue;
-    const long blocks = (long)a.max_frames * ((a.C / 8 + 63) / 64);
-    if (blocks <= 0) return submit_nothing(sk);
-    if (blocks > 0x7fffffffL) return hipErrorInvalidValue;
-    const void *k = bf16 ? reinterpret_cast<const void *>(&avgpool_kernel<u16>)
-                         : reinterpret_cast<const void *>(&avgpool_kernel<float>);
-    return submit(sk, k, dim3((unsigned)blocks, (unsigned)a.nseg), dim3(256), a);
+    if (!ew_ok(a, false) || a.C % 8 || a.H <= 0 || a.W <= 0 || (long)a.H * a.W > 0x3fffffffL) return hipErrorInvalidValue;
+    const int cw = a.C / 8 <= 4 ? 4 : 16;
+    const void *k = cw == 4 ? (bf16 ? reinterpret_cast<const void *>(&avgpool_kernel<u16, 4>)
+                                    : reinterpret_cast<const void *>(&avgpool_kernel<float, 4>))
+                            : (bf16 ? reinterpret_cast<const void *>(&avgpool_kernel<u16, 16>)
+                                    : reinterpret_cast<const void *>(&avgpool_kernel<float, 16>));
+    return frame_launch(k, (a.C / 8 + cw - 1) / cw, a, sk);
 }
 
 hipError_t launch_upsample2x(const EwArgs &a, bool bf16, const Sink &sk) {
     if (!ew_ok(a, false) || a.C % 8 || a.Ho != 2 * a.H || a.Wo != 2 * a.W) return hipErrorInvalidValue;
-    const long per = (long)a.Ho * a.Wo * (a.C / 8);
-    return bf16 ? ew_launch(reinterpret_cast<const void *>(&upsample2x_kernel<u16>), per, a, sk) : ew_launch(reinterpret_cast<const void *>(&upsample2x_kernel<float>), per, a, sk);
+    const void *k = bf16 ? reinterpret_cast<const void *>(&upsample2x_kernel<u16>)
+                         : reinterpret_cast<const void *>(&upsample2x_kernel<float>);
+    return item_launch(k, (long)a.Ho * a.Wo * (a.C / 8), a, sk);
 }
 
 hipError_t launch_concat(const EwArgs &a, bool bf16, const Sink &sk) {
     if (!ew_ok(a, true) || a.C % 8 || a.C1 % 8 || a.Co != a.C + a.C1) return hipErrorInvalidValue;
-    const long per = (long)a.H * a.W * (a.Co / 8);
-    return bf16 ? ew_launch(reinterpret_cast<const void *>(&concat_kernel<u16>), per, a, sk) : ew_launch(reinterpret_cast<const void *>(&concat_kernel<float>), per, a, sk);
+    const void *k = bf16 ? reinterpret_cast<const void *>(&concat_kernel<u16>)
+                         : reinterpret_cast<const void *>(&concat_kernel<float>);
+    return item_launch(k, (long)a.H * a.W * (a.Co / 8), a, sk);
 }
 
 hipError_t launch_export(const EwArgs &a, bool bf16, const Sink &sk) {
-    if (!ew_ok(a, false) || a.c_logical > a.C || a.c_logical <= 0) return hipErrorInvalidValue;
-    const long per = (long)((a.c_logical + 7) / 8) * a.H * a.W;
-    return bf16 ? ew_launch(reinterpret_cast<const void *>(&export_kernel<u16>), per, a, sk) : ew_launch(reinterpret_cast<const void *>(&export_kernel<float>), per, a, sk);
+    if (!ew_ok(a, false) || a.C % 8 || a.c_logical > a.C || a.c_logical <= 0) return hipErrorInvalidValue;
+    const long hw = (long)a.H * a.W;
+    if (hw > 0x3fffffffL) return hipErrorInvalidValue;
+    const void *k = bf16 ? reinterpret_cast<const void *>(&export_kernel<u16>)
+                         : reinterpret_cast<const void *>(&export_kernel<float>);
+    return frame_launch(k, (hw + 63) / 64 * ((a.c_logical + 63) / 64), a, sk);
 }
 
 }  // namespace gemel

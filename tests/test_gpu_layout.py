@@ -1,0 +1,70 @@
+"""Input pack, output export, pooling and routing kernels at the edges of
+their tiles: channel counts around 8 and 64, maps of one pixel, around 64
+pixels and of several workgroups, ragged frame counts over two models. Pack,
+upsample, max pool, concat and export move values without arithmetic, so
+bf16-representable inputs come back exactly; the average pool sums in
+float32 (a bf16 rounding, or (pixels + 2) * 2^-24 of the mean magnitude)."""
+
+import numpy as np
+import pytest
+
+from harness import GpuWorkload
+from test_gpu_layers import L
+from workloads.configs import ModelSpec, Workload
+
+pytestmark = pytest.mark.gpu
+
+MAPS = [(1, 1), (7, 7), (8, 8), (5, 13), (33, 40)]
+CHANNELS = [3, 8, 9, 24, 64, 72, 200]
+
+
+def run(layers, chw, frames, dtype):
+    ms = [ModelSpec(f"m{i}", "custom", layers, n, chw) for i, n in enumerate(frames)]
+    wl = Workload("layout", 23, dtype, ms, [], "normal")
+    fr = [wl.frames(i) for i in range(len(ms))]
+    g = GpuWorkload(wl)
+    try:
+        return fr, g.run(fr)
+    finally:
+        g.close()
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("hw", MAPS, ids=lambda m: f"{m[0]}x{m[1]}")
+@pytest.mark.parametrize("c", CHANNELS)
+def test_moved_values_are_exact(c, hw, dtype):
+    lay = [L("u", "upsample", -1, cin=c, cout=c, out=True),
+           L("p", "maxpool", 0, cin=c, cout=c, kh=3, kw=3, stride=2, pad=1, out=True),
+           L("q", "maxpool", 0, cin=c, cout=c, kh=2, kw=2, stride=2, out=True),
+           L("r", "maxpool", 0, cin=c, cout=c, kh=2, kw=2, stride=1, pad=1, out=True)]
+    if c % 8 == 0:
+        lay.append(L("k", "concat", 2, src1=1, cin=c, cout=2 * c, out=True))
+    fr, got = run(lay, (c,) + hw, [3, 1], dtype)
+    for x, outs in zip(fr, got):
+        up = x.repeat(2, 2).repeat(2, 3)
+        assert np.array_equal(outs[0], up)
+
+        def pool(k, s, p):
+            z = np.pad(up, ((0, 0), (0, 0), (p, p), (p, p)), constant_values=-np.inf)
+            v = np.lib.stride_tricks.sliding_window_view(z, (k, k), axis=(2, 3))
+            return v[:, :, ::s, ::s].max((4, 5))
+
+        assert np.array_equal(outs[1], pool(3, 2, 1))
+        assert np.array_equal(outs[2], x)
+        assert np.array_equal(outs[3], pool(2, 1, 1))
+        if c % 8 == 0:
+            assert np.array_equal(outs[4], np.concatenate([outs[2], outs[1]], 1))
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("c,hw", [(8, (1, 1)), (32, (16, 16)), (40, (7, 7)), (136, (3, 50)), (2048, (7, 7))])
+def test_average_pool(c, hw, dtype):
+    lay = [L("a", "avgpool", -1, cin=c, cout=c, out=True)]
+    fr, got = run(lay, (c,) + hw, [2, 5], dtype)
+    for x, outs in zip(fr, got):
+        ref = x.astype(np.float64).mean((2, 3), keepdims=True)
+        mag = np.abs(x.astype(np.float64)).mean((2, 3), keepdims=True)
+        bound = (hw[0] * hw[1] + 2) * 2.0 ** -24 * mag
+        if dtype == "bf16":
+            bound = bound + 2.0 ** -8 * (np.abs(ref) + bound)
+        assert np.all(np.abs(outs[0] - ref) <= bound)
