@@ -878,6 +878,24 @@ static gemel_status build_plan(gemel_ctx *ctx, const std::vector<int> &ids, cons
                     group_node[sig] = nid;
                 }
                 node_frames[nid] += nfr[(size_t)s];
+            } else if (ctx->opt.group_unmerged && L.op != GEMEL_OP_CONV && L.op != GEMEL_OP_FC && L.group < 0) {
+                // the same pooling or routing layer of several models behind
+                // one launch (a merged or grouped layer, or the input packs):
+                // one launch, a segment per model. Behind separate launches
+                // it stays separate, as one launch would join their chains.
+                auto producer = [&](int p) { return p < 0 ? -1 : node_of[(size_t)s][(size_t)p]; };
+                std::vector<int64_t> sig = {-2, L.op, L.in_h, L.in_w, L.in_phys, L.src1_phys, L.out_phys, L.out_h,
+                                            L.out_w, L.kh, L.stride, L.pad, producer(L.src0),
+                                            L.op == GEMEL_OP_CONCAT ? producer(L.src1) : -2};
+                sig.push_back(ungrouped_seen[{s, sig}]++);
+                auto it = group_node.find(sig);
+                if (it != group_node.end() && nodes[(size_t)it->second].mem.size() < GEMEL_MAX_SEG) {
+                    nid = it->second;
+                } else {
+                    nid = (int)nodes.size();
+                    nodes.push_back(Node{L.op, {}});
+                    group_node[sig] = nid;
+                }
             } else {
                 nid = (int)nodes.size();
                 nodes.push_back(Node{L.op, {}});
@@ -947,17 +965,31 @@ static gemel_status build_plan(gemel_ctx *ctx, const std::vector<int> &ids, cons
                     node_of[(size_t)s][p] = node_of[(size_t)s][(size_t)fused_into[(size_t)s][p]];
     }
 
-    // ---- steps: the ordered nodes, then one export step per output that is
-    // not written directly by its conv/FC epilogue ----
+    // ---- steps: the ordered nodes, then the exports of outputs that are not
+    // written directly by their conv/FC epilogue: one step per producing
+    // node and shape, a segment per output ----
     const int NN = (int)order.size();
     std::vector<int> pos(nodes.size());
     for (int i = 0; i < NN; ++i) pos[(size_t)order[(size_t)i]] = i;
-    std::vector<std::pair<int, int>> exports;  // (slot, layer)
-    for (int s = 0; s < S; ++s)
-        for (int l : model(s).outputs)
-            if (!direct_output(layer(s, l))) exports.push_back({s, l});
-    const int NS = NN + (int)exports.size();
     auto step_of = [&](int s, int l) { return pos[(size_t)node_of[(size_t)s][(size_t)l]]; };
+    std::vector<std::vector<std::pair<int, int>>> exports;  // members (slot, layer) of each
+    {
+        std::map<std::vector<int>, size_t> seen;
+        for (int s = 0; s < S; ++s)
+            for (int l : model(s).outputs) {
+                const Layer &L = layer(s, l);
+                if (direct_output(L)) continue;
+                const std::vector<int> key = {step_of(s, l), L.out_h, L.out_w, L.out_c, L.out_phys};
+                auto it = seen.find(key);
+                if (it != seen.end() && ctx->opt.group_unmerged && exports[it->second].size() < GEMEL_MAX_SEG) {
+                    exports[it->second].push_back({s, l});
+                } else {
+                    seen[key] = exports.size();
+                    exports.push_back({{s, l}});
+                }
+            }
+    }
+    const int NS = NN + (int)exports.size();
     std::vector<std::vector<int>> preds((size_t)NS);
     std::vector<double> est((size_t)NS, 5e-6);
     for (int i = 0; i < NN; ++i) {
@@ -980,7 +1012,8 @@ static gemel_status build_plan(gemel_ctx *ctx, const std::vector<int> &ids, cons
         }
         preds[(size_t)i].assign(ps.begin(), ps.end());
     }
-    for (size_t e = 0; e < exports.size(); ++e) preds[(size_t)NN + e] = {step_of(exports[e].first, exports[e].second)};
+    for (size_t e = 0; e < exports.size(); ++e)
+        preds[(size_t)NN + e] = {step_of(exports[e][0].first, exports[e][0].second)};
 
     // ---- happens-before: ancestors of each step in the dependency graph ----
     const size_t WDS = ((size_t)NS + 63) / 64;
@@ -1106,7 +1139,8 @@ static gemel_status build_plan(gemel_ctx *ctx, const std::vector<int> &ids, cons
             if (L.op == GEMEL_OP_CONCAT) use(s, L.src1, i);
             if (L.res >= 0) use(s, L.res, i);
         }
-    for (size_t e = 0; e < exports.size(); ++e) use(exports[e].first, exports[e].second, NN + (int)e);
+    for (size_t e = 0; e < exports.size(); ++e)
+        for (auto [s, l] : exports[e]) use(s, l, NN + (int)e);
     auto done_before = [&](const TInfo &t, const TInfo &u) {
         if (u.prod < 0) return false;
         if (t.users.empty()) return before(t.prod, u.prod);
@@ -1461,23 +1495,25 @@ static gemel_status build_plan(gemel_ctx *ctx, const std::vector<int> &ids, cons
     }
     // outputs that are also read internally (or not conv/fc): export to NCHW f32
     for (size_t e = 0; e < exports.size(); ++e) {
-        const auto [s, l] = exports[e];
-        const Layer &L = model(s).layers[(size_t)l];
         const size_t first_launch = P.launches.size();
         Launch Le;
         Le.type = L_EXPORT;
         Le.kind = GEMEL_K_EXPORT;
-        Le.bytes = (double)nfr[(size_t)s] * L.out_h * L.out_w * L.out_c * (esz + 4.0);
         Le.bf16 = bf16;
         EwArgs &a = Le.ew;
-        a.H = L.out_h; a.W = L.out_w; a.C = L.out_phys; a.c_logical = L.out_c;
-        a.nseg = 1;
-        a.seg[0].in0 = tptr(s, l);
-        a.seg[0].in1 = nullptr;
-        a.seg[0].out = nullptr;
-        a.seg[0].frames = nfr[(size_t)s];
-        a.max_frames = a.seg[0].frames;
-        Le.patches.push_back({Patch::OUTPUT, s, L.out_index, 0});
+        for (auto [s, l] : exports[e]) {
+            const Layer &L = layer(s, l);
+            a.H = L.out_h; a.W = L.out_w; a.C = L.out_phys; a.c_logical = L.out_c;
+            EwSeg &sg = a.seg[a.nseg];
+            sg.in0 = tptr(s, l);
+            sg.in1 = nullptr;
+            sg.out = nullptr;
+            sg.frames = nfr[(size_t)s];
+            a.max_frames = std::max(a.max_frames, sg.frames);
+            Le.bytes += (double)nfr[(size_t)s] * L.out_h * L.out_w * L.out_c * (esz + 4.0);
+            Le.patches.push_back({Patch::OUTPUT, s, L.out_index, a.nseg});
+            a.nseg++;
+        }
         P.launches.push_back(Le);
         tag_launches(first_launch, NN + (int)e);
     }

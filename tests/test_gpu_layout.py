@@ -68,3 +68,33 @@ def test_average_pool(c, hw, dtype):
         if dtype == "bf16":
             bound = bound + 2.0 ** -8 * (np.abs(ref) + bound)
         assert np.all(np.abs(outs[0] - ref) <= bound)
+
+
+@pytest.mark.parametrize("models", [2, 18], ids=["two", "more-than-a-launch-holds"])
+def test_pooling_and_routing_of_several_models_share_launches(models):
+    """The same pooling, routing and output layers behind one launch run as
+    one launch per kind, with the results of separate launches."""
+    from paper_2201_07705_amd import gemel as G
+    c, hw = 16, 10
+    lay = [L("p", "maxpool", -1, cin=c, cout=c, kh=2, kw=2, stride=2, out=True),
+           L("u", "upsample", 0, cin=c, cout=c),
+           L("k", "concat", 1, src1=-1, cin=c, cout=2 * c, out=True),
+           L("a", "avgpool", 2, cin=2 * c, cout=2 * c, out=True)]
+    ms = [ModelSpec(f"m{i}", "custom", lay, 1 + i % 3, (c, hw, hw)) for i in range(models)]
+    wl = Workload("share", 29, "bf16", ms, [], "normal")
+    fr = [wl.frames(i) for i in range(models)]
+    outs, launches = [], []
+    for group in (1, 0):
+        g = GpuWorkload(wl)
+        try:
+            g.ctx.set_option(G.OPT_GROUP_UNMERGED, group)
+            outs.append(g.run(fr, repeat=3))
+            launches.append(g.ctx.query(G.Q_LAUNCHES))
+        finally:
+            g.close()
+    for a, b in zip(*outs):
+        for x, y in zip(a, b):
+            assert np.array_equal(x, y)
+    packs = (models + 15) // 16
+    assert launches[1] == packs + 7 * models
+    assert launches[0] == packs + 7 * packs
