@@ -3,16 +3,22 @@
 // An FC layer at a few frames is a weight-streaming problem: every weight
 // byte is read once and used M times, far below the MFMA ridge point, so
 // the kernel is organised for HBM bandwidth. Each wave owns 16 output
-// neurons and a slice of K; every lane streams 64 contiguous bytes of one
-// weight row per step (4 lanes cover 256 contiguous bytes of a row) and the
-// same K positions of up to 16 frames, and v_mfma_f32_16x16x32_bf16 does the
-// multiply-adds (weights as the 16-row A operand, frames as the 16-column B
-// operand; the K order inside a step is the same for A and B, so any order
-// is correct). K is split over blockIdx.y so that enough waves are in flight
-// to saturate HBM; partial sums go to a [splits][M][N] fp32 buffer and the
-// last split of each column of 64 neurons to finish reduces them and
-// applies bias, activation and the store (or, without arrival counters,
-// fc_reduce does). With one split the epilogue is applied directly.
+// neurons and a slice of K. It streams its 16 weight rows through a ring of
+// LDS buffers of its own, by direct global-to-LDS loads of 256 contiguous
+// bytes per row, the steps ahead in flight while the oldest is read (no
+// barrier in the depth loop: a wave waits for its own loads only), and
+// v_mfma_f32_16x16x32_bf16 does the multiply-adds (weights as the 16-row A
+// operand, up to 16 frames as the 16-column B operand). K is split over
+// blockIdx.y so that enough waves are in flight to saturate HBM; partial
+// sums go to a [splits][M][N] fp32 buffer and the last split of each column
+// of 64 neurons to finish reduces them and applies bias, activation and the
+// store (or, without arrival counters, fc_reduce does). With one split the
+// epilogue is applied directly.
+//
+// Measured at 8 frames, against loads into registers inside per-lane bounds
+// checks (which the compiler waited for step by step): 25088 -> 4096 (205 MB)
+// 50-52 -> 41-46 us (4.9-4.4 TB/s), 4096 -> 4096 of two models (67 MB) 21.5
+// -> 17.3 us, 4096 -> 1000 12.5 -> 8.1 us, 4096 -> 10 9.9 -> 5.8 us.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -36,26 +42,31 @@ __device__ __forceinline__ float fc_act(float y, int act, float slope) {
     return act == 1 ? relu : act == 2 ? leaky : y;
 }
 
-// Segment holding launch frame f: the last one with f_start <= f.
-__device__ __forceinline__ int fc_seg(const FcArgs &a, int f) {
-    int s = 0;
-    for (int i = 1; i < a.nseg; ++i) s += (f >= a.seg[i].f_start) ? 1 : 0;
-    return s;
-}
-
-// Input row of launch frame f. A select walk over the segments with
-// constant indices: indexing the kernel-argument array with a computed
-// index would copy it to scratch memory.
-__device__ __forceinline__ const u16 *fc_in_row(const FcArgs &a, int f) {
-    const u16 *p = (const u16 *)a.seg[0].in + (size_t)f * a.K;
-#pragma unroll
-    for (int i = 1; i < GEMEL_MAX_SEG; ++i)
-        if (i < a.nseg && f >= a.seg[i].f_start) p = (const u16 *)a.seg[i].in + (size_t)(f - a.seg[i].f_start) * a.K;
-    return p;
+// Fields of the segment that holds launch frame f (the last one with f_start
+// <= f) by a select walk: the table lives in the argument block, which is
+// read with scalar loads; indexing it with a per-lane number makes every
+// field a dependent global load.
+struct FcRow {
+    const void *in;
+    void *out;
+    const float *scale, *shift;
+    int f_start;
+};
+__device__ __forceinline__ FcRow fc_row(const FcArgs &a, int f) {
+    FcRow r{a.seg[0].in, a.seg[0].out, a.seg[0].scale, a.seg[0].shift, 0};
+    for (int i = 1; i < a.nseg; ++i) {
+        const bool hit = f >= a.seg[i].f_start;
+        r.in = hit ? a.seg[i].in : r.in;
+        r.out = hit ? a.seg[i].out : r.out;
+        r.scale = hit ? a.seg[i].scale : r.scale;
+        r.shift = hit ? a.seg[i].shift : r.shift;
+        r.f_start = hit ? a.seg[i].f_start : r.f_start;
+    }
+    return r;
 }
 
 __device__ __forceinline__ void fc_store(const FcArgs &a, int f, int n, float acc, bool bf16) {
-    const FcSeg &sg = a.seg[fc_seg(a, f)];
+    const FcRow sg = fc_row(a, f);
     const int lf = f - sg.f_start;
     const float y = fc_act(acc * sg.scale[n] + sg.shift[n], a.act, a.slope);
     if (a.out_mode == OUT_NHWC) {
@@ -68,58 +79,74 @@ __device__ __forceinline__ void fc_store(const FcArgs &a, int f, int n, float ac
     }
 }
 
-// Elements of the LDS input slice: (depth per split) x (frames padded to
-// 16 per block), frame-minor, in runs of 64 16-byte slots. The planner
-// keeps MB * 16 * k_per_split within it with room for the last run.
-constexpr int FC_X_ELEMS = 32768;
+// vmcnt only: expcnt and lgkmcnt left at their maxima (gfx9 encoding).
+template <int N>
+__device__ __forceinline__ void fc_wait_vm() {
+    static_assert(N >= 0 && N < 16, "vmcnt range");
+    __builtin_amdgcn_s_waitcnt(N | (0x7 << 4) | (0xF << 8));
+}
+__device__ __forceinline__ void fc_wait_lgkm0() { __builtin_amdgcn_s_waitcnt(0xF | (0x3 << 14) | (0x7 << 4)); }
 
-// vmcnt(0) only: expcnt and lgkmcnt left at their maxima (gfx9 encoding).
-__device__ __forceinline__ void fc_wait_vm0() { __builtin_amdgcn_s_waitcnt((0x7 << 4) | (0xF << 8)); }
+// Depth of a ring step, and the 1 KB loads a wave makes for it (16 rows of
+// 256 bytes).
+constexpr int FC_KS = 128, FC_WI = 16 * FC_KS * 2 / 1024;
+// Ring buffers: with up to 16 frames three, so that two workgroups fit a CU
+// beside their input slices (48 + 28 KB each); beyond, four.
+constexpr int fc_stages(int mb) { return mb == 1 ? 3 : 4; }
 
 template <int MB>  // frame blocks of 16
 __global__ __launch_bounds__(256) void fc_bf16_kernel(const FcArgs a) {
     constexpr int COLS = 64;   // neurons of a workgroup, 16 per wave
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    constexpr int NST = fc_stages(MB);
+    __shared__ __attribute__((aligned(1024))) unsigned char r0[4 * FC_WI * 1024], r1[4 * FC_WI * 1024],
+        r2[4 * FC_WI * 1024], r3[NST > 3 ? 4 * FC_WI * 1024 : 16];
+    __shared__ __attribute__((aligned(16))) u16 xs[fc_x_elems(MB)];
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
     const int n0 = blockIdx.x * COLS + wave * 16;
     const int k_begin = blockIdx.y * a.k_per_split;
     const int k_end = min(a.K, k_begin + a.k_per_split);
-    const int g = lane >> 4;
+    const int g = lane >> 4, l16 = lane & 15;
     // frames [f0, f1) of this grid slice and their weights: every frame of
-    // the launch, or (grouped) segment blockIdx.z alone. A select walk with
-    // constant indices: indexing the kernel-argument array with a computed
-    // index would copy it to scratch memory.
+    // the launch, or (grouped) segment blockIdx.z alone
     const void *wsrc = a.w;
     int f0 = 0, f1 = a.M;
     if (a.grouped) {
         const int z = blockIdx.z;
-#pragma unroll
-        for (int i = 0; i < GEMEL_MAX_SEG; ++i) {
-            if (i == z) {
-                wsrc = a.seg[i].w;
-                f0 = a.seg[i].f_start;
-            }
-            if (i == z + 1 && i < a.nseg) f1 = a.seg[i].f_start;
+        for (int i = 0; i < a.nseg; ++i) {
+            wsrc = i == z ? a.seg[i].w : wsrc;
+            f0 = i == z ? a.seg[i].f_start : f0;
+            f1 = i == z + 1 ? a.seg[i].f_start : f1;
         }
     }
     const int mz = f1 - f0;
-    const int row = n0 + (lane & 15);
-    const bool row_ok = row < a.N;
-    const u16 *wrow = (const u16 *)wsrc + (size_t)(row_ok ? row : 0) * a.K;
-    // depth steps of 256: 8 weight chunks of 16 bytes per lane
-    // (lane g of a row covers 32 contiguous bytes of every 128), the next
-    // step's weights loaded while the current step's MFMAs run. The first
-    // step is requested before the input slice is staged, so that its
-    // latency overlaps the staging.
-    constexpr int KS = 256, WJ = KS / 32;
-    auto wload = [&](int k, uint4 (&wv)[WJ]) __attribute__((always_inline)) {
+    // load i of a step fills slots i * 64 + lane of the wave's buffer: row
+    // 4 i + lane / 16, whose 16-byte position lane % 16 holds chunk
+    // (lane % 16) ^ row (so that one chunk of 16 rows spans all banks). Rows
+    // beyond N read row N - 1 (never stored), chunks beyond k_end the last
+    // one of the slice (masked where they are used).
+    const u16 *wrow[FC_WI];
+    int wch[FC_WI];
 #pragma unroll
-        for (int j = 0; j < WJ; ++j) {
-            const int kk = k + j * 32 + g * 8;
-            wv[j] = (row_ok && kk < k_end) ? *(const uint4 *)(wrow + kk) : make_uint4(0, 0, 0, 0);
-        }
+    for (int i = 0; i < FC_WI; ++i) {
+        const int row = 4 * i + g;
+        wrow[i] = (const u16 *)wsrc + (size_t)min(n0 + row, a.N - 1) * a.K;
+        wch[i] = (l16 ^ row) * 8;
+    }
+    auto issue = [&](unsigned char *buf, int k) __attribute__((always_inline)) {
+#pragma unroll
+        for (int i = 0; i < FC_WI; ++i)
+            __builtin_amdgcn_global_load_lds((const void *)(wrow[i] + min(k + wch[i], k_end - 8)),
+                                             (fc_lds_u8 *)(buf + (wave * FC_WI + i) * 1024), 16, 0, 0);
     };
-    uint4 w0[WJ], w1[WJ];
-    if (n0 < a.N) wload(k_begin, w0);
+    unsigned char *const ring[4] = {r0, r1, r2, r3};
+    const int kn = k_end - k_begin;
+    const int steps = (kn + FC_KS - 1) / FC_KS;
+    // steps past the last one read its chunks again (into a buffer whose
+    // reads are over), so that the loop below has no branch around a load
+    const int k_last = k_begin + (steps - 1) * FC_KS;
+#pragma unroll
+    for (int s = 0; s < NST - 1; ++s) issue(ring[s], min(k_begin + s * FC_KS, k_last));
     // the workgroup's slice of the inputs, [k_begin, k_end) x frames, staged
     // in LDS once: every wave reads it, and from LDS its reads need no wait
     // on a global round trip inside the depth loop. With MP frames staged
@@ -131,54 +158,81 @@ __global__ __launch_bounds__(256) void fc_bf16_kernel(const FcArgs a) {
     // (each wave instruction writes 64 consecutive slots), all in flight at
     // once; staged frames beyond M repeat frame M - 1.
     const int MP = mz > 16 ? 16 * MB : mz > 8 ? 16 : mz > 4 ? 8 : mz > 2 ? 4 : mz;
-    __shared__ __attribute__((aligned(16))) u16 xs[FC_X_ELEMS];
-    const int kn = k_end - k_begin;
     {
         const int slots = (kn / 8) * MP;
         for (int s0 = wave * 64; s0 < slots; s0 += 256) {
             const int sl = min(s0 + lane, slots - 1);
             const int c = sl / MP, f = f0 + min(sl - c * MP, mz - 1);
-            __builtin_amdgcn_global_load_lds((const void *)(fc_in_row(a, f) + k_begin + c * 8),
-                                             (fc_lds_u8 *)(xs + s0 * 8), 16, 0, 0);
+            const FcRow r = fc_row(a, f);
+            __builtin_amdgcn_global_load_lds(
+                (const void *)((const u16 *)r.in + (size_t)(f - r.f_start) * a.K + k_begin + c * 8),
+                (fc_lds_u8 *)(xs + s0 * 8), 16, 0, 0);
         }
-        fc_wait_vm0();
+        fc_wait_vm<0>();
     }
     __syncthreads();
     f32x4 acc[MB];
 #pragma unroll
     for (int mb = 0; mb < MB; ++mb) acc[mb] = f32x4{0.f, 0.f, 0.f, 0.f};
 
-    auto step = [&](int k, const uint4 (&wv)[WJ]) __attribute__((always_inline)) {
+    constexpr int WJ = FC_KS / 32;
+    auto step = [&](const unsigned char *buf, int k, bool tail) __attribute__((always_inline)) {
+        uint4 wv[WJ];
+#pragma unroll
+        for (int j = 0; j < WJ; ++j)
+            wv[j] = *(const uint4 *)(buf + wave * FC_WI * 1024 + (l16 * 16 + ((j * 4 + g) ^ l16)) * 16);
+        uint4 xv[MB][WJ];
 #pragma unroll
         for (int mb = 0; mb < MB; ++mb) {
-            uint4 xv[WJ];
-            const int fr = mb * 16 + (lane & 15);
+            const int fr = mb * 16 + l16;
             const u16 *xr = xs + (fr < MP ? fr : (fr & (MP - 1))) * 8;
 #pragma unroll
-            for (int j = 0; j < WJ; ++j) {
-                const int kk = k + j * 32 + g * 8;
-                xv[j] = kk < k_end ? *(const uint4 *)(xr + ((kk - k_begin) >> 3) * MP * 8) : make_uint4(0, 0, 0, 0);
-            }
+            for (int j = 0; j < WJ; ++j)
+                xv[mb][j] = *(const uint4 *)(xr + ((min(k + j * 32 + g * 8, k_end - 8) - k_begin) >> 3) * MP * 8);
+        }
+        if (tail) {
 #pragma unroll
             for (int j = 0; j < WJ; ++j)
-                acc[mb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
-                    __builtin_bit_cast(bf16x8, wv[j]), __builtin_bit_cast(bf16x8, xv[j]), acc[mb], 0, 0, 0);
+                if (k + j * 32 + g * 8 >= k_end) {
+                    wv[j] = make_uint4(0, 0, 0, 0);
+#pragma unroll
+                    for (int mb = 0; mb < MB; ++mb) xv[mb][j] = make_uint4(0, 0, 0, 0);
+                }
         }
+#pragma unroll
+        for (int j = 0; j < WJ; ++j)
+#pragma unroll
+            for (int mb = 0; mb < MB; ++mb)
+                acc[mb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, wv[j]),
+                                                                  __builtin_bit_cast(bf16x8, xv[mb][j]), acc[mb], 0, 0, 0);
     };
     if (n0 < a.N) {
-        for (int k = k_begin; k < k_end; k += 2 * KS) {
-            if (k + KS < k_end) wload(k + KS, w1);
-            step(k, w0);
-            if (k + KS < k_end) {
-                if (k + 2 * KS < k_end) wload(k + 2 * KS, w0);
-                step(k + KS, w1);
-            }
+        auto turn = [&](int s, int k, bool tail) __attribute__((always_inline)) {
+            // step s has landed; the NST - 2 newer ones may fly. The
+            // refilled buffer was read in the step before.
+            fc_wait_vm<(NST - 2) * FC_WI>();
+            fc_wait_lgkm0();
+            issue(ring[(s + NST - 1) % NST], min(k + (NST - 1) * FC_KS, k_last));
+            __builtin_amdgcn_sched_barrier(0);
+            step(ring[s], k, tail);
+        };
+        // whole turns of the ring first, with no branch between the loads
+        // (the compiler's waits then see one path), then the last steps
+        const int full = kn / FC_KS;   // whole steps
+        int it = 0;
+        for (; it + NST <= full; it += NST) {
+#pragma unroll
+            for (int s = 0; s < NST; ++s) turn(s, k_begin + (it + s) * FC_KS, false);
         }
+#pragma unroll
+        for (int s = 0; s < NST; ++s)
+            if (it + s < steps) turn(s, k_begin + (it + s) * FC_KS, it + s >= full);
+        fc_wait_vm<0>();
     }
     // D[neuron = n0 + 4 g + v][frame = mb*16 + lane%16]
 #pragma unroll
     for (int mb = 0; mb < MB; ++mb) {
-        const int f = f0 + mb * 16 + (lane & 15);
+        const int f = f0 + mb * 16 + l16;
         if (f >= f1) continue;
 #pragma unroll
         for (int v = 0; v < 4; ++v) {
@@ -196,37 +250,35 @@ __global__ __launch_bounds__(256) void fc_bf16_kernel(const FcArgs a) {
         __shared__ int flag;
         if (!splitk_arrive(a.counters + (a.grouped ? blockIdx.z * gridDim.x : 0) + blockIdx.x, a.k_splits, &flag))
             return;
-        // four items per thread, eight splits per batch of loads
-        for (int i0 = threadIdx.x; i0 < mz * COLS; i0 += 4 * 256) {
-            float sum[4] = {0.f, 0.f, 0.f, 0.f};
-            bool ok[4];
-            const float *base[4];
+        // two items per thread, eight splits per batch of loads (at clamped
+        // addresses: a load inside a branch is waited for at its end)
+        const size_t split_elems = (size_t)a.M * a.N;
+        for (int i0 = threadIdx.x; i0 < mz * COLS; i0 += 2 * 256) {
+            float sum[2] = {0.f, 0.f};
+            int f[2], n[2];
+            const float *base[2];
 #pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                const int item = i0 + u * 256;
-                const int f = f0 + item / COLS, n = blockIdx.x * COLS + (item % COLS);
-                ok[u] = item < mz * COLS && n < a.N;
-                base[u] = a.partial + (ok[u] ? (size_t)f * a.N + n : 0);
+            for (int u = 0; u < 2; ++u) {
+                const int item = min(i0 + u * 256, mz * COLS - 1);
+                f[u] = f0 + item / COLS;
+                n[u] = blockIdx.x * COLS + item % COLS;
+                base[u] = a.partial + (size_t)f[u] * a.N + min(n[u], a.N - 1);
             }
-            const size_t split_elems = (size_t)a.M * a.N;
             for (int sp0 = 0; sp0 < a.k_splits; sp0 += 8) {
-                float p[4][8];
+                float p[2][8];
 #pragma unroll
-                for (int u = 0; u < 4; ++u)
-#pragma unroll
-                    for (int q = 0; q < 8; ++q)
-                        if (ok[u] && sp0 + q < a.k_splits) p[u][q] = load_partial1(base[u] + (sp0 + q) * split_elems);
-#pragma unroll
-                for (int u = 0; u < 4; ++u)
+                for (int u = 0; u < 2; ++u)
 #pragma unroll
                     for (int q = 0; q < 8; ++q)
-                        if (ok[u] && sp0 + q < a.k_splits) sum[u] += p[u][q];
+                        p[u][q] = load_partial1(base[u] + min(sp0 + q, a.k_splits - 1) * split_elems);
+#pragma unroll
+                for (int u = 0; u < 2; ++u)
+#pragma unroll
+                    for (int q = 0; q < 8; ++q) sum[u] += sp0 + q < a.k_splits ? p[u][q] : 0.f;
             }
 #pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                const int item = i0 + u * 256;
-                if (ok[u]) fc_store(a, f0 + item / COLS, blockIdx.x * COLS + (item % COLS), sum[u], true);
-            }
+            for (int u = 0; u < 2; ++u)
+                if (i0 + u * 256 < mz * COLS && n[u] < a.N) fc_store(a, f[u], n[u], sum[u], true);
         }
     }
 }
@@ -274,7 +326,7 @@ hipError_t launch_fc_bf16(const FcArgs &a, const Sink &sk) {
         // LDS slots of the input slice, rounded up to whole 64-slot runs
         const int mp = ms > 16 ? (ms + 15) / 16 * 16 : ms > 8 ? 16 : ms > 4 ? 8 : ms > 2 ? 4 : ms;
         const long slots = (long)std::min(a.K, a.k_per_split) / 8 * mp;
-        if ((slots + 63) / 64 * 64 * 8 > FC_X_ELEMS) return hipErrorInvalidValue;
+        if ((slots + 63) / 64 * 64 * 8 > fc_x_elems((ms + 15) / 16)) return hipErrorInvalidValue;
     }
     dim3 grid((unsigned)((a.N + 63) / 64), (unsigned)a.k_splits, (unsigned)(a.grouped ? a.nseg : 1)), block(256);
     const int mb = (ms + 15) / 16;

@@ -125,6 +125,10 @@ hipError_t launch_conv_reduce(const ReduceArgs &a, bool bf16, const Sink &sk);
 hipError_t static_scratch(int device, void **ptr);
 hipError_t launch_fill_u32(uint32_t *p, size_t n, uint32_t v, const Sink &sk);
 
+// Elements of the FC kernel's LDS input slice for `mb` blocks of 16 frames:
+// (depth per split) x (frames padded to a power of two, or to 16 per block),
+// with room for the last run of 64 16-byte slots.
+constexpr int fc_x_elems(int mb) { return mb <= 1 ? 14336 : 32768; }
 hipError_t launch_fc_bf16(const FcArgs &a, const Sink &sk);
 hipError_t launch_fc_reduce(const FcArgs &a, bool bf16, const Sink &sk);
 
