@@ -95,7 +95,10 @@ __global__ __launch_bounds__(64 * WM *WN, (dma_min_waves<BM, BN, WM, WN, STAGES,
     constexpr int RPI = 64 / CPR;                               // rows per DMA instruction
     constexpr int TM = BM / WM, TN = BN / WN;
     constexpr int FM = TM / 16, FN = TN / 16;
-    constexpr int A_SLOTS = BM * CPR, B_SLOTS = BN * CPR;      // 16-byte slots per stage
+    // 16-byte slots per stage; the rows of A are loaded by whole
+    // instructions of the workgroup (rows beyond BM, which no fragment
+    // reads, come from the zero page)
+    constexpr int A_SLOTS = (BM * CPR + NT - 1) / NT * NT, B_SLOTS = BN * CPR;
     constexpr int AI = A_SLOTS / NT, BI = B_SLOTS / NT;        // DMA instructions per thread
     static_assert(AI * NT == A_SLOTS && BI * NT == B_SLOTS && AI >= 1 && BI >= 1, "tile/threads");
     constexpr int STAGE_BYTES = (A_SLOTS + B_SLOTS) * 16;
@@ -104,6 +107,10 @@ __global__ __launch_bounds__(64 * WM *WN, (dma_min_waves<BM, BN, WM, WN, STAGES,
     static_assert(TN % 8 == 0 && 64 % (TN / 8) == 0 && TN <= 512,
                   "every epilogue item of a lane is the same 8-channel chunk of its wave's columns");
     constexpr int PER_STEP = AI + BI;                           // vm ops per thread per step
+    // the phased loop (below, the 224 x 256 tile): its fragments and
+    // accumulators take 176 of a lane's 256 registers, so it keeps the
+    // loader's state small (256 rows did not fit: 40 to 100 bytes of scratch)
+    constexpr bool PHASED = STAGES == 2 && BK == 64 && NT == 512 && FM == 7;
     __shared__ __attribute__((aligned(1024))) unsigned char st0[STAGE_BYTES];
     __shared__ __attribute__((aligned(1024))) unsigned char st1[STAGE_BYTES];
     __shared__ __attribute__((aligned(1024))) unsigned char st2[STAGES > 2 ? STAGE_BYTES : 16];
@@ -191,7 +198,8 @@ __global__ __launch_bounds__(64 * WM *WN, (dma_min_waves<BM, BN, WM, WN, STAGES,
             aH[i] = 0;
             aW[i] = 0;
         }
-        if (hetero && gm < m_end) {
+        const bool row_ok = gm < m_end && (A_SLOTS == BM * CPR || rl < BM);
+        if (hetero && row_ok) {
             // the row's segment sizes: uniform in a tile inside one segment,
             // else gathered with scalar loads and selects like row_seg
             int sH = a.seg[s_first].H, sW = a.seg[s_first].W, sHo = a.seg[s_first].Ho, sWo = a.seg[s_first].Wo;
@@ -211,7 +219,7 @@ __global__ __launch_bounds__(64 * WM *WN, (dma_min_waves<BM, BN, WM, WN, STAGES,
             awi[i] = (pix - ho * sWo) * a.stride - a.pad;
             aH[i] = sH;
             aW[i] = sW;
-        } else if (gm < m_end) {
+        } else if (row_ok) {
             int fr, ho, wo;
             // quotients by multiply-high (the launcher's magic numbers): a
             // per-lane integer division costs dozens of instructions
@@ -237,12 +245,17 @@ __global__ __launch_bounds__(64 * WM *WN, (dma_min_waves<BM, BN, WM, WN, STAGES,
         }
     }
     // weight rows beyond N read row 0 instead (their columns are never stored)
-    const u16 *bbase[BI];
+    // (PHASED: 32-bit byte offsets from the weights' base)
+    const u16 *bbase[PHASED ? 1 : BI];
+    uint32_t boff32[PHASED ? BI : 1];
 #pragma unroll
     for (int i = 0; i < BI; ++i) {
         const int rl = (i * NW + wave) * RPI + lane / CPR;
         const int gn = tn * BN + rl;
-        bbase[i] = (const u16 *)wseg + (size_t)(gn < N ? gn : 0) * K + ((lane % CPR) ^ sw(rl)) * 8;
+        if constexpr (PHASED)
+            boff32[i] = ((uint32_t)(gn < N ? gn : 0) * (uint32_t)K + ((lane % CPR) ^ sw(rl)) * 8) * 2;
+        else
+            bbase[i] = (const u16 *)wseg + (size_t)(gn < N ? gn : 0) * K + ((lane % CPR) ^ sw(rl)) * 8;
     }
     // loader position (uniform): next step's tap (lr, ls) and channel base lc
     int kb = k_begin, lc, lr, ls;
@@ -256,31 +269,58 @@ __global__ __launch_bounds__(64 * WM *WN, (dma_min_waves<BM, BN, WM, WN, STAGES,
     // pixel, or the zero page where the tap falls outside the image (or the
     // row beyond M). Recomputed when the tap changes; a depth step only adds
     // the uniform channel offset (the zero page spans any row's channels).
+    // (PHASED: the tap's pixel itself, moved by the taps' uniform distance,
+    // and one bit per row for whether it lies in the image)
     const u16 *arow[AI];
+    uint32_t inside = 0;
+    if constexpr (PHASED) {
+#pragma unroll
+        for (int i = 0; i < AI; ++i)
+            arow[i] = abase[i] + ((ptrdiff_t)(ahi[i] + lr) * (hetero ? aW[hetero ? i : 0] : W) + awi[i] + ls) * in_cs +
+                      acq[i] * 8;
+    }
     auto set_tap = [&]() __attribute__((always_inline)) {
+        if constexpr (PHASED) inside = 0;
 #pragma unroll
         for (int i = 0; i < AI; ++i) {
             const int hi = ahi[i] + lr, wi = awi[i] + ls;
             const int Hr = hetero ? aH[hetero ? i : 0] : H, Wr = hetero ? aW[hetero ? i : 0] : W;
             const bool ok = (unsigned)hi < (unsigned)Hr && (unsigned)wi < (unsigned)Wr;
-            arow[i] = (ok ? abase[i] + (size_t)(hi * Wr + wi) * in_cs : zp) + acq[i] * 8;
+            if constexpr (PHASED)
+                inside |= ok ? 1u << i : 0u;
+            else
+                arow[i] = (ok ? abase[i] + (size_t)(hi * Wr + wi) * in_cs : zp) + acq[i] * 8;
         }
     };
     set_tap();
     auto issue = [&](unsigned char *stage) __attribute__((always_inline)) {
 #pragma unroll
-        for (int i = 0; i < AI; ++i)
-            __builtin_amdgcn_global_load_lds((const void *)(arow[i] + lc), (lds_u8 *)(stage + (i * NW + wave) * 1024),
-                                             16, 0, 0);
+        for (int i = 0; i < AI; ++i) {
+            const u16 *p = arow[i];
+            if constexpr (PHASED) p = (inside >> i) & 1 ? p : zp;
+            __builtin_amdgcn_global_load_lds((const void *)(p + lc), (lds_u8 *)(stage + (i * NW + wave) * 1024), 16, 0,
+                                             0);
+        }
 #pragma unroll
-        for (int i = 0; i < BI; ++i)
-            __builtin_amdgcn_global_load_lds((const void *)(bbase[i] + kb),
-                                             (lds_u8 *)(stage + A_SLOTS * 16 + (i * NW + wave) * 1024), 16, 0, 0);
+        for (int i = 0; i < BI; ++i) {
+            const void *p;
+            if constexpr (PHASED)
+                p = (const char *)((const u16 *)wseg + kb) + boff32[i];
+            else
+                p = bbase[i] + kb;
+            __builtin_amdgcn_global_load_lds(p, (lds_u8 *)(stage + A_SLOTS * 16 + (i * NW + wave) * 1024), 16, 0, 0);
+        }
         kb += BK;
         lc += BK;
         if (lc == Cin) {
             lc = 0;
-            if (++ls == kw) { ls = 0; ++lr; }
+            const bool wrap = ++ls == kw;
+            if constexpr (PHASED) {
+#pragma unroll
+                for (int i = 0; i < AI; ++i)
+                    arow[i] += wrap ? ((hetero ? aW[hetero ? i : 0] : W) - (kw - 1)) * in_cs : in_cs;
+            }
+            if (wrap) { ls = 0; ++lr; }
             set_tap();
         }
     };
@@ -332,28 +372,119 @@ __global__ __launch_bounds__(64 * WM *WN, (dma_min_waves<BM, BN, WM, WN, STAGES,
     };
 
     // epilogue constants of this lane's 8 channels (every segment shares
-    // one scale/shift pair), fetched ahead of the depth loop
+    // one scale/shift pair), fetched ahead of the depth loop (PHASED: after
+    // it, where the fragments' registers are free)
     const int my_gn = tn * BN + wn * TN + (lane % (TN / 8)) * 8;
     f32x4 sc0 = {1.f, 1.f, 1.f, 1.f}, sc1 = sc0, sh0 = {0.f, 0.f, 0.f, 0.f}, sh1 = sh0;
-    if (a.k_splits <= 1 && my_gn < N) {
-        const float *scl = useg.scale + my_gn, *shl = useg.shift + my_gn;
-        sc0 = *(const f32x4 *)scl;
-        sc1 = *(const f32x4 *)(scl + 4);
-        sh0 = *(const f32x4 *)shl;
-        sh1 = *(const f32x4 *)(shl + 4);
-    }
+    auto load_affine = [&]() __attribute__((always_inline)) {
+        if (a.k_splits <= 1 && my_gn < N) {
+            const float *scl = useg.scale + my_gn, *shl = useg.shift + my_gn;
+            sc0 = *(const f32x4 *)scl;
+            sc1 = *(const f32x4 *)(scl + 4);
+            sh0 = *(const f32x4 *)shl;
+            sh1 = *(const f32x4 *)(shl + 4);
+        }
+    };
+    if constexpr (!PHASED) load_affine();
 
     const int nk = (k_end - k_begin) / BK;
     unsigned char *const stg[4] = {st0, st1, st2, st3};
+    if constexpr (!PHASED) {
 #pragma unroll
-    for (int s = 0; s < STAGES - 1; ++s)
-        if (s < nk) issue(stg[s]);
+        for (int s = 0; s < STAGES - 1; ++s)
+            if (s < nk) issue(stg[s]);
+    }
 
     // register double-buffering needs a second fragment set: only where it
     // fits beside the accumulators (512-thread workgroups have 256
     // registers per lane)
     constexpr bool PIPE = STAGES == 4 && (NT <= 256 || FM * FN <= 16);
-    if constexpr (PIPE) {
+    if constexpr (PHASED) {
+        // Two stages of depth 64 and 8 waves (two per SIMD) of 7 x 4
+        // fragments. A step is a row of phases (two halves of 32 depths x
+        // groups of G0 fragment rows), and each phase reads the fragments of
+        // the next one from LDS before its own MFMAs, so that the LDS reads
+        // of a step (176 KB, about as many cycles as its MFMAs) run beside
+        // them. The one barrier of a step stands before
+        // its last phase: every wave has then read all of the step's stage
+        // (its last fragments arrived) and its own loads of the next stage
+        // have landed, so the stage is refilled for step s + 2 (a whole
+        // step of time to land) and the next stage's first fragments are
+        // read under the last phase's MFMAs.
+        constexpr int G0 = (FM + 1) / 2;
+        constexpr int NG = (FM + G0 - 1) / G0, NP = 2 * NG;
+        bf16x8 fa[2][G0], fb[2][FN];
+        // fragments of phase P (its B fragments with a half's first group)
+        auto rd = [&](const unsigned char *stage, auto pc) __attribute__((always_inline)) {
+            constexpr int P = decltype(pc)::value, h = P / NG, grp = P % NG;
+            const int pos = ((h * 4 + g) ^ swl) * 16;
+            if constexpr (grp == 0) {
+#pragma unroll
+                for (int j = 0; j < FN; ++j) fb[h][j] = *(const bf16x8 *)(stage + boff[j] + pos);
+            }
+            StaticFor<G0>::run([&](auto ic) __attribute__((always_inline)) {
+                constexpr int i = decltype(ic)::value;
+                if constexpr (grp * G0 + i < FM) fa[P & 1][i] = *(const bf16x8 *)(stage + aoff[grp * G0 + i] + pos);
+            });
+        };
+        auto mm = [&](auto pc) __attribute__((always_inline)) {
+            constexpr int P = decltype(pc)::value, h = P / NG, grp = P % NG;
+            StaticFor<G0>::run([&](auto ic) __attribute__((always_inline)) {
+                constexpr int i = decltype(ic)::value;
+                if constexpr (grp * G0 + i < FM) {
+#pragma unroll
+                    for (int j = 0; j < FN; ++j)
+                        acc[grp * G0 + i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fa[P & 1][i], fb[h][j],
+                                                                                       acc[grp * G0 + i][j], 0, 0, 0);
+                }
+            });
+            __builtin_amdgcn_sched_barrier(0);
+        };
+        // the phases of a step over stage cur; more: a next step exists (in
+        // nxt), refill: one after it does
+        auto do_step = [&](unsigned char *cur, unsigned char *nxt, bool more, bool refill) __attribute__((always_inline)) {
+            StaticFor<NP - 1>::run([&](auto pc) __attribute__((always_inline)) {
+                rd(cur, std::integral_constant<int, decltype(pc)::value + 1>{});
+                mm(pc);
+            });
+            wait_lgkm0();
+            if (more) {
+                wait_vm<0>();
+                __builtin_amdgcn_s_barrier();
+                if (refill) issue(cur);
+                __builtin_amdgcn_sched_barrier(0);
+                rd(nxt, std::integral_constant<int, 0>{});
+            }
+            mm(std::integral_constant<int, NP - 1>{});
+        };
+        // a prologue of its own for the steady loop, without branches: the
+        // compiler's waits then see one path into it (merged with the short
+        // one, it drained every load at the top of the loop)
+        int it = 0;
+        if (nk >= 4) {
+            issue(st0);
+            issue(st1);
+            wait_vm<PER_STEP>();
+            __builtin_amdgcn_s_barrier();
+            __builtin_amdgcn_sched_barrier(0);
+            rd(st0, std::integral_constant<int, 0>{});
+            do {
+                do_step(st0, st1, true, true);
+                do_step(st1, st0, true, true);
+                it += 2;
+            } while (it + 3 < nk);
+        } else if (nk > 0) {
+            issue(st0);
+            if (nk > 1) issue(st1);
+            wait_steps<PER_STEP, 2>(min(nk - 1, 1));
+            __builtin_amdgcn_s_barrier();
+            rd(st0, std::integral_constant<int, 0>{});
+        }
+        for (; it < nk; it += 2) {
+            do_step(st0, st1, it + 1 < nk, it + 2 < nk);
+            if (it + 1 < nk) do_step(st1, st0, it + 2 < nk, it + 3 < nk);
+        }
+    } else if constexpr (PIPE) {
         // Fragments double-buffered in registers: iteration it reads step
         // it+1's fragments from LDS, then issues step it's MFMAs from the
         // registers filled one iteration earlier, so the LDS reads overlap
@@ -439,6 +570,7 @@ __global__ __launch_bounds__(64 * WM *WN, (dma_min_waves<BM, BN, WM, WN, STAGES,
     constexpr int CHW = TN / 8;                                 // 8-channel chunks per wave row
     constexpr int ITEMS = PG * 16 * CHW / 64;                    // (row, chunk) items per lane per group
     static_assert(ITEMS * 64 == PG * 16 * CHW, "items per lane");
+    if constexpr (PHASED) load_affine();
     wait_vm<0>();
     __builtin_amdgcn_s_barrier();
     const int sidx = wave % STAGES;
@@ -639,8 +771,22 @@ hipError_t launch_conv_dma(const ConvArgs &a, int tile, const Sink &sk) {
         if (s.H <= 0 || s.W <= 0 || s.Ho <= 0 || s.Wo <= 0 || rows <= 0 || rows % ((long)s.Ho * s.Wo))
             return hipErrorInvalidValue;
     }
-    const int bm = conv_tile_bm(tile), bn = conv_tile_bn(tile);
+    int bm = conv_tile_bm(tile), bn = conv_tile_bn(tile);
     if (!bm) return hipErrorInvalidValue;
+    // the 256 x 256 tile of depth 64 has one workgroup on a CU: 224 rows
+    // where that fills the CUs' last turn better (49 * 2^k rows, the usual
+    // batches of 224-pixel frames, are 196 tiles of 256 rows on 256 CUs, or
+    // 224 of 224 rows: M 50176, N 256, K 2304 takes 58-61 us instead of
+    // 63-66 us, K 1152 38.5 instead of 44 us, 1.0 and 0.77 PFLOP/s)
+    const int mode = a.out_mode == OUT_NHWC_POOL2 ? 1 : a.hetero ? 2 : 0;
+    bool rows224 = false;
+    // (its weights are addressed with 32-bit byte offsets)
+    if (tile == TILE_DMA64_256x256 && (long)a.N * a.K * 2 > 0xffffffffL) tile = TILE_DMA_256x256;
+    if (tile == TILE_DMA64_256x256 && !a.grouped && a.k_splits == 1) {
+        auto turns = [&](long rows) { return ((a.M + rows - 1) / rows * ((a.N + 255) / 256) + 255) / 256 * rows; };
+        rows224 = turns(224) < turns(256);
+    }
+    if (rows224) bm = 224;
     // grouped: each segment tiled on its own, from tile seg[s].t_start
     ConvArgs b = a;
     long tiles = 0;
@@ -675,7 +821,6 @@ hipError_t launch_conv_dma(const ConvArgs &a, int tile, const Sink &sk) {
     }
     dim3 grid((unsigned)blocks, (unsigned)a.k_splits);
     hipError_t e = hipErrorInvalidValue;
-    const int mode = a.out_mode == OUT_NHWC_POOL2 ? 1 : a.hetero ? 2 : 0;
 #define GEMEL_DMA_CASE(T, BM_, BN_, WM_, WN_, ST_, BK_, NT_)                                                  \
     case T:                                                                                                   \
         e = submit(sk,                                                                                        \
@@ -684,7 +829,8 @@ hipError_t launch_conv_dma(const ConvArgs &a, int tile, const Sink &sk) {
                                : reinterpret_cast<const void *>(&conv_dma_kernel<BM_, BN_, WM_, WN_, ST_, BK_, 0>), \
                    grid, dim3(NT_), b);                                                                       \
         break;
-    switch (tile) {
+    switch (rows224 ? TILE_COUNT : tile) {
+        GEMEL_DMA_CASE(TILE_COUNT, 224, 256, 2, 4, 2, 64, 512)
         GEMEL_DMA_CASE(TILE_DMA_256x256, 256, 256, 2, 4, 4, 32, 512)
         GEMEL_DMA_CASE(TILE_DMA_256x128, 256, 128, 2, 2, 4, 32, 256)
         GEMEL_DMA_CASE(TILE_DMA_128x128, 128, 128, 2, 2, 4, 32, 256)
