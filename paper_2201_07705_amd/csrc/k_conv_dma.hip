@@ -107,6 +107,12 @@ __global__ __launch_bounds__(64 * WM *WN, (dma_min_waves<BM, BN, WM, WN, STAGES,
     static_assert(TN % 8 == 0 && 64 % (TN / 8) == 0 && TN <= 512,
                   "every epilogue item of a lane is the same 8-channel chunk of its wave's columns");
     constexpr int PER_STEP = AI + BI;                           // vm ops per thread per step
+    // register double-buffered fragments (below): only where a second
+    // fragment set fits beside the accumulators (512-thread workgroups have
+    // 256 registers per lane). A stage's fragments are then in registers
+    // before its MFMAs start, so every stage can be in flight.
+    constexpr bool PIPE = STAGES == 4 && (NT <= 256 || FM * FN <= 16);
+    constexpr int AHEAD = PIPE ? STAGES : STAGES - 1;           // steps requested before the depth loop
     // the phased loop (below, the 224 x 256 tile): its fragments and
     // accumulators take 176 of a lane's 256 registers, so it keeps the
     // loader's state small (256 rows did not fit: 40 to 100 bytes of scratch)
@@ -156,8 +162,51 @@ __global__ __launch_bounds__(64 * WM *WN, (dma_min_waves<BM, BN, WM, WN, STAGES,
     if (t >= tiles) return;
     const int k_begin = blockIdx.y * a.k_per_split;
     const int k_end = min(a.K, k_begin + a.k_per_split);
+    const int N = a.N, K = a.K;
+    const int nk = (k_end - k_begin) / BK;
+
+    // ---- DMA assignment: instruction i of this thread fills slot
+    // (i*NW + wave)*64 + lane: row (i*NW + wave)*RPI + lane/CPR; the slot's
+    // chunk position lane%CPR holds logical chunk (lane%CPR) ^ sw(row) ----
+    auto sw = [](int row) __attribute__((always_inline)) { return (row >> 1) & (CPR - 1); };
+    // weight rows beyond N read row 0 instead (their columns are never stored)
+    // (PHASED: 32-bit byte offsets from the weights' base)
+    const u16 *bbase[PHASED ? 1 : BI];
+    uint32_t boff32[PHASED ? BI : 1];
+#pragma unroll
+    for (int i = 0; i < BI; ++i) {
+        const int rl = (i * NW + wave) * RPI + lane / CPR;
+        const int gn = tn * BN + rl;
+        if constexpr (PHASED)
+            boff32[i] = ((uint32_t)(gn < N ? gn : 0) * (uint32_t)K + ((lane % CPR) ^ sw(rl)) * 8) * 2;
+        else
+            bbase[i] = (const u16 *)wseg + (size_t)(gn < N ? gn : 0) * K + ((lane % CPR) ^ sw(rl)) * 8;
+    }
+    int kb = k_begin;   // next step's depth of the weight loads
+    auto issue_b = [&](unsigned char *stage) __attribute__((always_inline)) {
+#pragma unroll
+        for (int i = 0; i < BI; ++i) {
+            const void *p;
+            if constexpr (PHASED)
+                p = (const char *)((const u16 *)wseg + kb) + boff32[i];
+            else
+                p = bbase[i] + kb;
+            __builtin_amdgcn_global_load_lds(p, (lds_u8 *)(stage + A_SLOTS * 16 + (i * NW + wave) * 1024), 16, 0, 0);
+        }
+        kb += BK;
+    };
+    // the weights of the first two steps are requested before the input rows
+    // are worked out: their addresses are few, and they often come from HBM,
+    // whose latency then passes under the row arithmetic
+    constexpr int EARLY = AHEAD < 2 ? AHEAD : 2;
+    unsigned char *const stg[4] = {st0, st1, st2, st3};
+    if constexpr (!PHASED) {
+#pragma unroll
+        for (int s = 0; s < EARLY; ++s)
+            if (s < nk) issue_b(stg[s]);
+    }
     const int HWo = a.Ho * a.Wo;
-    const int H = a.H, W = a.W, in_cs = a.in_cs, N = a.N, K = a.K, Cin = a.Cin, kw = a.kw;
+    const int H = a.H, W = a.W, in_cs = a.in_cs, Cin = a.Cin, kw = a.kw;
     const size_t frame_elems = (size_t)H * W * in_cs;
     const u16 *const zp = (const u16 *)a.zero;
     // segment of the tile's first and last row (wave-uniform, scalar loads):
@@ -171,11 +220,12 @@ __global__ __launch_bounds__(64 * WM *WN, (dma_min_waves<BM, BN, WM, WN, STAGES,
     }
     const bool one_seg = s_first == s_last;
     const RowSeg useg = uni_seg(a, s_first);
+    // (the walk out of the way of the usual path: every line of a kernel's
+    // code that runs is fetched anew at most launches)
+    auto seg_of = [&](int gm) __attribute__((always_inline)) {
+        return __builtin_expect(one_seg, 1) ? useg : row_seg(a, gm);
+    };
 
-    // ---- DMA assignment: instruction i of this thread fills slot
-    // (i*NW + wave)*64 + lane: row (i*NW + wave)*RPI + lane/CPR; the slot's
-    // chunk position lane%CPR holds logical chunk (lane%CPR) ^ sw(row) ----
-    auto sw = [](int row) __attribute__((always_inline)) { return (row >> 1) & (CPR - 1); };
     // with the 2x2 max pool fused, rows run over the output in window
     // order: row 4g + 2dy + dx is pixel (2hp + dy, 2wp + dx) of pooled pixel g
     constexpr bool pool2 = MODE == 1;
@@ -211,7 +261,7 @@ __global__ __launch_bounds__(64 * WM *WN, (dma_min_waves<BM, BN, WM, WN, STAGES,
                     sHo = hit ? a.seg[k].Ho : sHo;
                     sWo = hit ? a.seg[k].Wo : sWo;
                 }
-            const RowSeg sg = one_seg ? useg : row_seg(a, gm);
+            const RowSeg sg = seg_of(gm);
             const int local = gm - sg.m_start, hw = sHo * sWo;
             const int fl = local / hw, pix = local - fl * hw, ho = pix / sWo;
             abase[i] = (const u16 *)sg.in + (size_t)fl * sH * sW * in_cs;
@@ -238,27 +288,14 @@ __global__ __launch_bounds__(64 * WM *WN, (dma_min_waves<BM, BN, WM, WN, STAGES,
                 ho = qdiv(pix, 1);
                 wo = pix - ho * a.Wo;
             }
-            const RowSeg sg = one_seg ? useg : row_seg(a, gm);
+            const RowSeg sg = seg_of(gm);
             abase[i] = (const u16 *)sg.in + (size_t)(fr - sg.f_start) * frame_elems;
             ahi[i] = ho * a.stride - a.pad;
             awi[i] = wo * a.stride - a.pad;
         }
     }
-    // weight rows beyond N read row 0 instead (their columns are never stored)
-    // (PHASED: 32-bit byte offsets from the weights' base)
-    const u16 *bbase[PHASED ? 1 : BI];
-    uint32_t boff32[PHASED ? BI : 1];
-#pragma unroll
-    for (int i = 0; i < BI; ++i) {
-        const int rl = (i * NW + wave) * RPI + lane / CPR;
-        const int gn = tn * BN + rl;
-        if constexpr (PHASED)
-            boff32[i] = ((uint32_t)(gn < N ? gn : 0) * (uint32_t)K + ((lane % CPR) ^ sw(rl)) * 8) * 2;
-        else
-            bbase[i] = (const u16 *)wseg + (size_t)(gn < N ? gn : 0) * K + ((lane % CPR) ^ sw(rl)) * 8;
-    }
     // loader position (uniform): next step's tap (lr, ls) and channel base lc
-    int kb = k_begin, lc, lr, ls;
+    int lc, lr, ls;
     {
         const int rs = k_begin / Cin;
         lc = k_begin - rs * Cin;
@@ -293,7 +330,7 @@ __global__ __launch_bounds__(64 * WM *WN, (dma_min_waves<BM, BN, WM, WN, STAGES,
         }
     };
     set_tap();
-    auto issue = [&](unsigned char *stage) __attribute__((always_inline)) {
+    auto issue_a = [&](unsigned char *stage) __attribute__((always_inline)) {
 #pragma unroll
         for (int i = 0; i < AI; ++i) {
             const u16 *p = arow[i];
@@ -301,16 +338,6 @@ __global__ __launch_bounds__(64 * WM *WN, (dma_min_waves<BM, BN, WM, WN, STAGES,
             __builtin_amdgcn_global_load_lds((const void *)(p + lc), (lds_u8 *)(stage + (i * NW + wave) * 1024), 16, 0,
                                              0);
         }
-#pragma unroll
-        for (int i = 0; i < BI; ++i) {
-            const void *p;
-            if constexpr (PHASED)
-                p = (const char *)((const u16 *)wseg + kb) + boff32[i];
-            else
-                p = bbase[i] + kb;
-            __builtin_amdgcn_global_load_lds(p, (lds_u8 *)(stage + A_SLOTS * 16 + (i * NW + wave) * 1024), 16, 0, 0);
-        }
-        kb += BK;
         lc += BK;
         if (lc == Cin) {
             lc = 0;
@@ -323,6 +350,10 @@ __global__ __launch_bounds__(64 * WM *WN, (dma_min_waves<BM, BN, WM, WN, STAGES,
             if (wrap) { ls = 0; ++lr; }
             set_tap();
         }
+    };
+    auto issue = [&](unsigned char *stage) __attribute__((always_inline)) {
+        issue_a(stage);
+        issue_b(stage);
     };
 
     f32x4 acc[FM][FN];
@@ -387,18 +418,31 @@ __global__ __launch_bounds__(64 * WM *WN, (dma_min_waves<BM, BN, WM, WN, STAGES,
     };
     if constexpr (!PHASED) load_affine();
 
-    const int nk = (k_end - k_begin) / BK;
-    unsigned char *const stg[4] = {st0, st1, st2, st3};
-    if constexpr (!PHASED) {
+    // the inputs of the first steps, and the weights beyond the early ones: a
+    // step's loads are in flight in the order inputs, weights, but for the
+    // early weights, which are older than everything here. Step 0 must then
+    // land: behind its inputs, the second step's inputs and the whole steps
+    // after it may fly (the waits of the loops below count whole steps
+    // behind the one they need).
+    auto prologue = [&]() __attribute__((always_inline)) {
 #pragma unroll
-        for (int s = 0; s < STAGES - 1; ++s)
-            if (s < nk) issue(stg[s]);
-    }
+        for (int s = 0; s < AHEAD; ++s)
+            if (s < nk) {
+                if (s < EARLY)
+                    issue_a(stg[s]);
+                else
+                    issue(stg[s]);
+            }
+        if (AHEAD > 3 && nk > 3)
+            wait_vm<AI + 2 * PER_STEP>();
+        else if (AHEAD > 2 && nk > 2)
+            wait_vm<AI + PER_STEP>();
+        else if (AHEAD > 1 && nk > 1)
+            wait_vm<AI>();
+        else
+            wait_vm<0>();
+    };
 
-    // register double-buffering needs a second fragment set: only where it
-    // fits beside the accumulators (512-thread workgroups have 256
-    // registers per lane)
-    constexpr bool PIPE = STAGES == 4 && (NT <= 256 || FM * FN <= 16);
     if constexpr (PHASED) {
         // Two stages of depth 64 and 8 waves (two per SIMD) of 7 x 4
         // fragments. A step is a row of phases (two halves of 32 depths x
@@ -488,31 +532,50 @@ __global__ __launch_bounds__(64 * WM *WN, (dma_min_waves<BM, BN, WM, WN, STAGES,
         // Fragments double-buffered in registers: iteration it reads step
         // it+1's fragments from LDS, then issues step it's MFMAs from the
         // registers filled one iteration earlier, so the LDS reads overlap
-        // the MFMAs. The DMA issued in iteration it refills the buffer of
-        // step it-1, whose fragments every wave read before this
-        // iteration's barrier.
+        // the MFMAs. Step it's fragments have then left its stage: once
+        // every wave has passed this iteration's barrier, the stage is
+        // refilled for step it+STAGES, and STAGES-1 steps are in flight (a
+        // small tile's step takes the latency of a load divided by the steps
+        // in flight: LDS and MFMAs are idle for most of it). With STAGES-2
+        // steps in flight before: M 3136, N 256, K 2304 13.9 -> 12.1 us, M 784,
+        // N 512, K 2048 15.7 -> 12.7 us (weights from HBM).
         FragA fa[2];
         FragB fb[2];
-        if (nk > 0) {
-            // steps 0 .. min(nk, STAGES-1)-1 were issued; step 0 must land
-            wait_steps<PER_STEP, STAGES - 1>(min(nk - 1, STAGES - 2));
+        int base = 0;
+        if (nk >= STAGES) {
+            // the prologue without its branches: the compiler's waits then
+            // see one path into the loop (merged with the short one, it
+            // drained every load before the first step)
+            issue_a(stg[0]);
+            issue_a(stg[1]);
+            issue(stg[2]);
+            issue(stg[3]);
+            wait_vm<AI + 2 * PER_STEP>();
+            __builtin_amdgcn_s_barrier();
+            __builtin_amdgcn_sched_barrier(0);
+            read_frags(stg[0], fa[0], fb[0]);
+            // steady state: every iteration of the group waits, issues the
+            // DMA STAGES steps ahead and reads the next fragments (no
+            // branches here either). The fragments read one iteration ago
+            // (the operands of the MFMAs) have long arrived: waiting for
+            // them before the barrier frees their stage, and keeps the
+            // compiler from waiting for them after the next reads.
+            if (base + 2 * STAGES <= nk) do {
+#pragma unroll
+                for (int s = 0; s < STAGES; ++s) {
+                    wait_lgkm0();
+                    wait_vm<(STAGES - 2) * PER_STEP>();
+                    __builtin_amdgcn_s_barrier();
+                    issue(stg[s]);
+                    read_frags(stg[(s + 1) % STAGES], fa[(s + 1) & 1], fb[(s + 1) & 1]);
+                    mfmas(fa[s & 1], fb[s & 1]);
+                }
+                base += STAGES;
+            } while (base + 2 * STAGES <= nk);
+        } else if (nk > 0) {
+            prologue();
             __builtin_amdgcn_s_barrier();
             read_frags(stg[0], fa[0], fb[0]);
-        }
-        int base = 0;
-        // steady state: every iteration of the group waits, issues the DMA
-        // STAGES-1 steps ahead and reads the next fragments (no branches, so
-        // the compiler's wait placement sees one path)
-        for (; base + 2 * STAGES - 1 <= nk; base += STAGES) {
-#pragma unroll
-            for (int s = 0; s < STAGES; ++s) {
-                wait_vm<(STAGES - 3) * PER_STEP>();
-                __builtin_amdgcn_s_barrier();
-                issue(stg[(s + STAGES - 1) % STAGES]);
-                wait_lgkm0();
-                read_frags(stg[(s + 1) % STAGES], fa[(s + 1) & 1], fb[(s + 1) & 1]);
-                mfmas(fa[s & 1], fb[s & 1]);
-            }
         }
         // the last groups, with the bounds checks
         for (; base < nk; base += STAGES) {
@@ -520,26 +583,21 @@ __global__ __launch_bounds__(64 * WM *WN, (dma_min_waves<BM, BN, WM, WN, STAGES,
             for (int s = 0; s < STAGES; ++s) {
                 const int it = base + s;
                 if (it < nk) {
+                    wait_lgkm0();   // on both paths: no read pending on the MFMAs' operands
                     if (it + 1 < nk) {
                         // step it+1 must have landed; the newer steps issued
-                        // (up to it+STAGES-2, none beyond nk-1) may fly
-                        wait_steps<PER_STEP, STAGES - 2>(min(nk - it - 2, STAGES - 3));
+                        // (up to it+STAGES-1, none beyond nk-1) may fly
+                        wait_steps<PER_STEP, STAGES - 1>(min(nk - it - 2, STAGES - 2));
                         __builtin_amdgcn_s_barrier();
-                        if (it + STAGES - 1 < nk) issue(stg[(s + STAGES - 1) % STAGES]);
-                        // the fragments read one iteration ago (the operands
-                        // of the MFMAs below) have long arrived: waiting for
-                        // them here, before the next reads are issued, keeps
-                        // the compiler from waiting for those after them
-                        wait_lgkm0();
+                        if (it + STAGES < nk) issue(stg[s]);
                         read_frags(stg[(s + 1) % STAGES], fa[(s + 1) & 1], fb[(s + 1) & 1]);
-                    } else {
-                        wait_lgkm0();   // both paths reach the MFMAs with no read pending on their operands
                     }
                     mfmas(fa[s & 1], fb[s & 1]);
                 }
             }
         }
     } else {
+        prologue();
         // main loop, unrolled by STAGES so that every buffer index is static
         for (int base = 0; base < nk; base += STAGES) {
 #pragma unroll
@@ -596,7 +654,7 @@ __global__ __launch_bounds__(64 * WM *WN, (dma_min_waves<BM, BN, WM, WN, STAGES,
             rv[u] = u32x4{0u, 0u, 0u, 0u};
             const int gm = row0 + (lane + u * 64) / CHW;
             if (pre_res && col_ok && gm < m_end) {
-                const RowSeg sg = one_seg ? useg : row_seg(a, gm);
+                const RowSeg sg = seg_of(gm);
                 rv[u] = *(const u32x4 *)((const u16 *)sg.res + (size_t)(gm - sg.m_start) * out_cs + gn);
             }
         }
@@ -621,9 +679,9 @@ __global__ __launch_bounds__(64 * WM *WN, (dma_min_waves<BM, BN, WM, WN, STAGES,
         // here, once: with none pending, the compiler needs no wait between
         // the stores below (vmcnt counts loads and stores together, so a
         // wait for a load would also wait for every earlier store). Without
-        // a residual nothing is waited for: the epilogue kinds without one
-        // never read the residual registers.
-        if (pre_res) wait_vm<0>();
+        // a residual too: a wait under a branch leaves it believing that
+        // loads are pending, and it waited before each store instead.
+        wait_vm<0>();
         if constexpr (pool2) {
             // pooled items (window, chunk): the window's 4 staged rows through
             // the epilogue, each rounded to bf16 as stored unfused, then their
@@ -648,7 +706,7 @@ __global__ __launch_bounds__(64 * WM *WN, (dma_min_waves<BM, BN, WM, WN, STAGES,
 #pragma unroll
                     for (int j = 0; j < 8; ++j) mx[j] = fmaxf(mx[j], bf2f(f2bf(y[j])));
                 }
-                const RowSeg sg = one_seg ? useg : row_seg(a, gm);
+                const RowSeg sg = seg_of(gm);
                 *(u32x4 *)((u16 *)sg.out + (size_t)((gm - sg.m_start) >> 2) * out_cs + gn) = pack8_bf16(mx);
             }
         } else {
@@ -666,7 +724,7 @@ __global__ __launch_bounds__(64 * WM *WN, (dma_min_waves<BM, BN, WM, WN, STAGES,
                 continue;
             }
             const float v[8] = {v0.x, v0.y, v0.z, v0.w, v1.x, v1.y, v1.z, v1.w};
-            const RowSeg sg = one_seg ? useg : row_seg(a, gm);
+            const RowSeg sg = seg_of(gm);
             float y[8];
             epi8_f32(v, s8, h8, rv[u], ekind, a.has_res, a.res_mode, a.act, a.slope, y);
             if (planes) {   // back to the staging, for the pass below
@@ -688,7 +746,7 @@ __global__ __launch_bounds__(64 * WM *WN, (dma_min_waves<BM, BN, WM, WN, STAGES,
             __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
             const int rl = lane % R, gm = row0 + rl;
             if (gm < m_end) {
-                const RowSeg sg = one_seg ? useg : row_seg(a, gm);
+                const RowSeg sg = seg_of(gm);
                 const int lr_ = gm - sg.m_start;
                 const int f = lr_ / HWo, pix = lr_ - f * HWo;
                 int c = tn * BN + wn * TN + lane / R * 4;
@@ -777,12 +835,14 @@ hipError_t launch_conv_dma(const ConvArgs &a, int tile, const Sink &sk) {
     // where that fills the CUs' last turn better (49 * 2^k rows, the usual
     // batches of 224-pixel frames, are 196 tiles of 256 rows on 256 CUs, or
     // 224 of 224 rows: M 50176, N 256, K 2304 takes 58-61 us instead of
-    // 63-66 us, K 1152 38.5 instead of 44 us, 1.0 and 0.77 PFLOP/s)
+    // 63-66 us, K 1152 38.5 instead of 44 us, 1.0 and 0.77 PFLOP/s); not with
+    // segments of several map sizes, whose row walk leaves that tile no
+    // registers
     const int mode = a.out_mode == OUT_NHWC_POOL2 ? 1 : a.hetero ? 2 : 0;
     bool rows224 = false;
     // (its weights are addressed with 32-bit byte offsets)
     if (tile == TILE_DMA64_256x256 && (long)a.N * a.K * 2 > 0xffffffffL) tile = TILE_DMA_256x256;
-    if (tile == TILE_DMA64_256x256 && !a.grouped && a.k_splits == 1) {
+    if (tile == TILE_DMA64_256x256 && !a.grouped && !a.hetero && a.k_splits == 1) {
         auto turns = [&](long rows) { return ((a.M + rows - 1) / rows * ((a.N + 255) / 256) + 255) / 256 * rows; };
         rows224 = turns(224) < turns(256);
     }
@@ -830,7 +890,12 @@ hipError_t launch_conv_dma(const ConvArgs &a, int tile, const Sink &sk) {
                    grid, dim3(NT_), b);                                                                       \
         break;
     switch (rows224 ? TILE_COUNT : tile) {
-        GEMEL_DMA_CASE(TILE_COUNT, 224, 256, 2, 4, 2, 64, 512)
+    case TILE_COUNT:
+        e = submit(sk,
+                   mode == 1 ? reinterpret_cast<const void *>(&conv_dma_kernel<224, 256, 2, 4, 2, 64, 1>)
+                             : reinterpret_cast<const void *>(&conv_dma_kernel<224, 256, 2, 4, 2, 64, 0>),
+                   grid, dim3(512), b);
+        break;
         GEMEL_DMA_CASE(TILE_DMA_256x256, 256, 256, 2, 4, 4, 32, 512)
         GEMEL_DMA_CASE(TILE_DMA_256x128, 256, 128, 2, 2, 4, 32, 256)
         GEMEL_DMA_CASE(TILE_DMA_128x128, 128, 128, 2, 2, 4, 32, 256)
