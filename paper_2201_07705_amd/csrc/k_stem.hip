@@ -6,10 +6,13 @@
 // 16x16x32 MFMA operand (one 16-byte chunk) are exactly one filter tap of
 // one pixel, so both operands are loaded straight from global memory into
 // registers (no im2col). With 64-channel tiles the weight fragments are
-// staged in LDS once per workgroup instead (all four waves use the same
-// ones; fetched by every wave they are two thirds of the loads, 5% of the
-// time measured on the VGG and ResNet stems; with 32-channel tiles the
-// staging costs more than it saves). A depth step of 32 covers 4 taps
+// staged in LDS once per workgroup instead (all waves use the same ones;
+// fetched by every wave they are two thirds of the loads; with 32-channel
+// tiles the staging costs more than it saves), by direct global-to-LDS loads
+// that are all in flight at once: through registers a loop waited out one
+// latency per 4 KB (7x7 stem, 16 frames of 224 x 224: 30-34 us before,
+// 23-25 now; what remains is the latency of two turns of workgroups, the
+// traffic taking 8 us). A depth step of 32 covers 4 taps
 // (the last step of a filter is padded with zero taps). The weight
 // fragment is the MFMA's first operand and the pixel fragment its second,
 // so a lane's result is 4 output channels of one pixel. The weight rows of
@@ -19,8 +22,8 @@
 // writes (NCHW output). Epilogue scale/shift (one pair of arrays shared by
 // every segment) are fetched together once the depth loop ends.
 //
-// Tile: 4 waves x PF 16-pixel fragments by NF 16-channel fragments: 64
-// channels (PF 2) or 32 (PF 4) per workgroup, so that a pixel's output
+// Tile: NW (4 or 8) waves x PF 16-pixel fragments by NF 16-channel fragments:
+// 64 channels (PF 2) or 32 (PF 4) per workgroup, so that a pixel's output
 // channels are written whole by one workgroup. The depth loop loads step
 // k+1 while the MFMAs of step k run; with three steps (3x3 filters) every
 // load is issued before the first MFMA.
@@ -39,6 +42,7 @@ typedef unsigned short u16;
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
+typedef __attribute__((address_space(3))) uint8_t lds_u8;
 
 __device__ __forceinline__ float s_bf2f(u16 h) { return __uint_as_float((uint32_t)h << 16); }
 __device__ __forceinline__ u16 s_f2bf(float f) { return __builtin_bit_cast(u16, (__bf16)f); }
@@ -71,9 +75,9 @@ struct SFor<0> {
 
 }  // namespace
 
-template <int PF, int NF, int S>
-__global__ __launch_bounds__(256) void conv_stem_kernel(const ConvArgs a) {
-    constexpr int BN = NF * 16, STEM_PX = 4 * PF * 16;
+template <int PF, int NF, int S, int NW>
+__global__ __launch_bounds__(NW * 64) void conv_stem_kernel(const ConvArgs a) {
+    constexpr int BN = NF * 16, STEM_PX = NW * PF * 16;
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int tiles_n = (a.N + BN - 1) / BN;
@@ -185,13 +189,28 @@ __global__ __launch_bounds__(256) void conv_stem_kernel(const ConvArgs a) {
     });
     auto stage_weights = [&]() __attribute__((always_inline)) {
         if constexpr (!WLDS) return;
-        for (int e = threadIdx.x; e < steps * NF * 64; e += 256) {
-            const int l = e & 63, sj = e >> 6, st = sj / NF, J = sj - (sj / NF) * NF;
+        // fragment sj = step * NF + J is 64 lanes' chunks in a row, one direct
+        // global-to-LDS load of a wave: every load is in flight at once (a
+        // loop through registers waits out one latency per pass)
+        const int r16 = ((l16 >> 2) * 8) + (l16 & 3);
+        auto stage = [&](int sj) __attribute__((always_inline)) {
+            const int st = sj / NF, J = sj % NF;
             // MFMA row r of fragment J holds channel 32*(J/2) + 8*(r/4) + 4*(J%2) + r%4
-            const int n = tn * BN + (J / 2) * 32 + ((l & 15) >> 2) * 8 + (J % 2) * 4 + (l & 3);
-            const int tap = st * 4 + (l >> 4);
-            wl[e] = *(const bf16x8 *)((n < N && tap < taps) ? (const u16 *)a.w + (size_t)n * K + tap * 8 : zp);
+            const int n = tn * BN + (J / 2) * 32 + (J % 2) * 4 + r16;
+            const int tap = st * 4 + kq;
+            const u16 *p = (n < N && tap < taps) ? (const u16 *)a.w + (size_t)n * K + tap * 8 : zp;
+            __builtin_amdgcn_global_load_lds((const void *)p, (lds_u8 *)(wl + sj * 64), 16, 0, 0);
+        };
+        if constexpr (S > 0) {
+            constexpr int FULL = S * NF / NW, REST = S * NF % NW;
+            SFor<FULL>::run([&](auto i) __attribute__((always_inline)) { stage(i * NW + wave); });
+            if (wave < REST) stage(FULL * NW + wave);
+        } else {
+            for (int sj = wave; sj < steps * NF; sj += NW) stage(sj);
         }
+        // the loads into LDS are counted by vmcnt: each wave waits for its own
+        // before the barrier
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
         __syncthreads();
     };
     auto read_w = [&](int step, bf16x8 (&wf)[NF]) __attribute__((always_inline)) {
@@ -389,19 +408,26 @@ hipError_t launch_conv_stem(const ConvArgs &a, const Sink &sk) {
     // more: 2 x 4 (a wider tile holds its pixels' whole output rows; 4 x 4
     // would spill registers)
     const bool narrow = a.N <= 32;
-    const int px = narrow ? 256 : 128, bn = narrow ? 32 : 64;
+    const int steps = (a.kh * a.kw + 3) / 4;
+    // the 13-step filter's weights take 52 KB of LDS, so three workgroups of 4
+    // waves share a CU (12 waves, under the 16 that the registers allow).
+    // Rounds of more 128-pixel tiles than that (768) take 8 waves per
+    // workgroup: two share a CU (16 waves) and each weight staging serves
+    // twice the pixels; fewer tiles spread further with 4
+    const bool w8 = !narrow && steps == 13 && (long)((a.M + 127) / 128) * ((a.N + 63) / 64) > 768;
+    const int px = narrow || w8 ? 256 : 128, bn = narrow ? 32 : 64;
     const long tiles = (long)((a.M + px - 1) / px) * ((a.N + bn - 1) / bn);
     const long blocks = tiles >= 8 ? (tiles + 7) / 8 * 8 : tiles;
     if (blocks > 0x7fffffffL) return hipErrorInvalidValue;
-    const dim3 grid((unsigned)blocks), block(256);
+    const dim3 grid((unsigned)blocks), block(w8 ? 512 : 256);
     // straight-line forms for 3 and 13 depth steps (3x3 and 7x7 filters)
-    const int steps = (a.kh * a.kw + 3) / 4;
-    const void *k = narrow ? (steps == 3    ? reinterpret_cast<const void *>(&conv_stem_kernel<4, 2, 3>)
-                              : steps == 13 ? reinterpret_cast<const void *>(&conv_stem_kernel<4, 2, 13>)
-                                            : reinterpret_cast<const void *>(&conv_stem_kernel<4, 2, 0>))
-                           : (steps == 3    ? reinterpret_cast<const void *>(&conv_stem_kernel<2, 4, 3>)
-                              : steps == 13 ? reinterpret_cast<const void *>(&conv_stem_kernel<2, 4, 13>)
-                                            : reinterpret_cast<const void *>(&conv_stem_kernel<2, 4, 0>));
+    const void *k = narrow ? (steps == 3    ? reinterpret_cast<const void *>(&conv_stem_kernel<4, 2, 3, 4>)
+                              : steps == 13 ? reinterpret_cast<const void *>(&conv_stem_kernel<4, 2, 13, 4>)
+                                            : reinterpret_cast<const void *>(&conv_stem_kernel<4, 2, 0, 4>))
+                           : (steps == 3    ? reinterpret_cast<const void *>(&conv_stem_kernel<2, 4, 3, 4>)
+                              : w8          ? reinterpret_cast<const void *>(&conv_stem_kernel<2, 4, 13, 8>)
+                           : steps == 13 ? reinterpret_cast<const void *>(&conv_stem_kernel<2, 4, 13, 4>)
+                                            : reinterpret_cast<const void *>(&conv_stem_kernel<2, 4, 0, 4>));
     return submit(sk, k, grid, block, a);
 }
 

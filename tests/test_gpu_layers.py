@@ -416,3 +416,17 @@ def test_grouped_unmerged_fc_exact(case, fused):
     for a, b in zip(outs[0], outs[1]):
         for x, y in zip(a, b):
             assert np.array_equal(x, y)
+
+
+@pytest.mark.parametrize("chw,stride,frames", [
+    ((3, 128, 256), 1, [3]),       # 768 tiles of 128 pixels: 4 waves
+    ((3, 129, 256), 1, [3]),       # 774: 8 waves
+    ((3, 181, 182), 1, [2, 1]),    # 8 waves, a tile across two models' frames, a ragged last tile
+    ((3, 363, 361), 2, [1, 2]),    # the same, stride 2
+], ids=lambda v: "x".join(map(str, v)) if isinstance(v, (list, tuple)) else str(v))
+def test_stem_7x7_waves_per_workgroup(chw, stride, frames):
+    log(f"stem {chw} {stride} {frames}")
+    lay = [conv("c", -1, 3, 64, 7, stride, 3, bn=True, act="relu"),
+           L("p", "maxpool", 0, cin=64, cout=64, kh=3, kw=3, stride=2, pad=1, out=True)]
+    groups = [[(m, 0) for m in range(len(frames))]] if len(frames) > 1 else []
+    run_case([lay] * len(frames), chw, frames, "bf16", groups)
