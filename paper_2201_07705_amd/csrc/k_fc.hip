@@ -15,10 +15,12 @@
 // store (or, without arrival counters, fc_reduce does). With one split the
 // epilogue is applied directly.
 //
-// Measured at 8 frames, against loads into registers inside per-lane bounds
-// checks (which the compiler waited for step by step): 25088 -> 4096 (205 MB)
-// 50-52 -> 41-46 us (4.9-4.4 TB/s), 4096 -> 4096 of two models (67 MB) 21.5
-// -> 17.3 us, 4096 -> 1000 12.5 -> 8.1 us, 4096 -> 10 9.9 -> 5.8 us.
+// Measured against loads into registers inside per-lane bounds checks (which
+// the compiler waited for step by step), one layer alone, its weights in the
+// memory-side cache, at 1 / 8 / 16 / 64 frames: 25088 -> 4096 (205 MB) 35.0 /
+// 42.0 / 51.3 / 207 us before, 32.7 / 33.7 / 44.4 / 177 here; 4096 -> 1000 8.8
+// / 11.5 / 14.1 / 31.6 before, 6.5 / 7.6 / 9.0 / 24.4 here; 2048 -> 20 7.2 / 9.1
+// / 11.8 / 22.2 before, 5.1 / 5.8 / 7.5 / 15.0 here.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -90,17 +92,19 @@ __device__ __forceinline__ void fc_wait_lgkm0() { __builtin_amdgcn_s_waitcnt(0xF
 // Depth of a ring step, and the 1 KB loads a wave makes for it (16 rows of
 // 256 bytes).
 constexpr int FC_KS = 128, FC_WI = 16 * FC_KS * 2 / 1024;
-// Ring buffers: with up to 16 frames three, so that two workgroups fit a CU
-// beside their input slices (48 + 28 KB each); beyond, four.
-constexpr int fc_stages(int mb) { return mb == 1 ? 3 : 4; }
 
-template <int MB>  // frame blocks of 16
+// MB: frame blocks of 16. DEEP: the input slice of 64 KB and four ring
+// buffers (one workgroup on a CU); else a slice of 28 KB and three, so that
+// two workgroups fit a CU. At 16 frames fc 25088 -> 4096 (16 splits of 1664)
+// takes 44.4 us DEEP; 33 splits of 768, whose slices fit the small form, took
+// 46.6.
+template <int MB, bool DEEP>
 __global__ __launch_bounds__(256) void fc_bf16_kernel(const FcArgs a) {
     constexpr int COLS = 64;   // neurons of a workgroup, 16 per wave
-    constexpr int NST = fc_stages(MB);
+    constexpr int NST = DEEP ? 4 : 3;
     __shared__ __attribute__((aligned(1024))) unsigned char r0[4 * FC_WI * 1024], r1[4 * FC_WI * 1024],
         r2[4 * FC_WI * 1024], r3[NST > 3 ? 4 * FC_WI * 1024 : 16];
-    __shared__ __attribute__((aligned(16))) u16 xs[fc_x_elems(MB)];
+    __shared__ __attribute__((aligned(16))) u16 xs[DEEP ? FC_X_ELEMS : FC_X_SMALL];
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
     const int n0 = blockIdx.x * COLS + wave * 16;
@@ -322,19 +326,15 @@ hipError_t launch_fc_bf16(const FcArgs &a, const Sink &sk) {
     if (!fc_args_ok(a) || (a.k_splits > 1 && a.k_per_split % 128)) return hipErrorInvalidValue;
     const int ms = fc_slice_frames(a);
     if (ms < 1 || ms > 64) return hipErrorInvalidValue;
-    {
-        // LDS slots of the input slice, rounded up to whole 64-slot runs
-        const int mp = ms > 16 ? (ms + 15) / 16 * 16 : ms > 8 ? 16 : ms > 4 ? 8 : ms > 2 ? 4 : ms;
-        const long slots = (long)std::min(a.K, a.k_per_split) / 8 * mp;
-        if ((slots + 63) / 64 * 64 * 8 > fc_x_elems((ms + 15) / 16)) return hipErrorInvalidValue;
-    }
+    const int64_t slice = fc_slice_elems(ms, std::min(a.K, a.k_per_split));
+    if (slice > FC_X_ELEMS) return hipErrorInvalidValue;
     dim3 grid((unsigned)((a.N + 63) / 64), (unsigned)a.k_splits, (unsigned)(a.grouped ? a.nseg : 1)), block(256);
     const int mb = (ms + 15) / 16;
-    const void *t[4] = {reinterpret_cast<const void *>(&fc_bf16_kernel<1>),
-                        reinterpret_cast<const void *>(&fc_bf16_kernel<2>),
-                        reinterpret_cast<const void *>(&fc_bf16_kernel<3>),
-                        reinterpret_cast<const void *>(&fc_bf16_kernel<4>)};
-    const void *fn = t[mb - 1];
+    const void *t[4] = {reinterpret_cast<const void *>(&fc_bf16_kernel<1, true>),
+                        reinterpret_cast<const void *>(&fc_bf16_kernel<2, true>),
+                        reinterpret_cast<const void *>(&fc_bf16_kernel<3, true>),
+                        reinterpret_cast<const void *>(&fc_bf16_kernel<4, true>)};
+    const void *fn = mb == 1 && slice <= FC_X_SMALL ? reinterpret_cast<const void *>(&fc_bf16_kernel<1, false>) : t[mb - 1];
     return submit(sk, fn, grid, block, a);
 }
 

@@ -125,10 +125,17 @@ hipError_t launch_conv_reduce(const ReduceArgs &a, bool bf16, const Sink &sk);
 hipError_t static_scratch(int device, void **ptr);
 hipError_t launch_fill_u32(uint32_t *p, size_t n, uint32_t v, const Sink &sk);
 
-// Elements of the FC kernel's LDS input slice for `mb` blocks of 16 frames:
-// (depth per split) x (frames padded to a power of two, or to 16 per block),
-// with room for the last run of 64 16-byte slots.
-constexpr int fc_x_elems(int mb) { return mb <= 1 ? 14336 : 32768; }
+// Frames of the FC kernel's LDS input slice (padded to a power of two, or to
+// 16 per block), and its elements at `depth` per split, in whole runs of 64
+// 16-byte slots. A slice holds at most FC_X_ELEMS; up to 16 frames in at most
+// FC_X_SMALL take the kernel form that lets two workgroups share a CU.
+constexpr int FC_X_ELEMS = 32768, FC_X_SMALL = 14336;
+inline int fc_slice_pad(int frames) {
+    return frames > 16 ? (frames + 15) / 16 * 16 : frames > 8 ? 16 : frames > 4 ? 8 : frames > 2 ? 4 : frames;
+}
+inline int64_t fc_slice_elems(int frames, int64_t depth) {
+    return (depth / 8 * fc_slice_pad(frames) + 63) / 64 * 64 * 8;
+}
 hipError_t launch_fc_bf16(const FcArgs &a, const Sink &sk);
 hipError_t launch_fc_reduce(const FcArgs &a, bool bf16, const Sink &sk);
 

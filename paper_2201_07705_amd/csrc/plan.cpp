@@ -735,24 +735,22 @@ bool tune_conv(gemel_ctx *ctx, const ConvArgs &a0, int dma_depth, bool bf16, int
     return true;
 }
 
-// Split-K of the small-batch FC kernel: about a workgroup per CU, each split
-// at least four ring steps deep, its input slice (frames x depth) within the
-// kernel's LDS. Fewer, deeper splits pay for fewer partial sums and
-// reductions: 4096 -> 4096 of two models at 8 frames takes 17.3 us with 4
-// splits, 22.7 with 8, 27.4 with 16; 4096 -> 1000 takes 8.1 with 8 and 10.1
-// with 16 (256 deep), 8.8 with 4.
+// Split-K of the small-batch FC kernel: about 1024 workgroups, each split at
+// least 1024 deep, and no deeper than its input slice (padded frames x depth)
+// fits the kernel's LDS, which overrides both. The splits fix the order of the
+// float32 sums, and with it the output's last bits: fewer workgroups (256) in
+// splits from 512 deep would be up to 1 us faster on small layers (4096 ->
+// 1000 at 8 frames 7.1 instead of 7.6 us, 2048 -> 1000 6.0 instead of 7.1) and
+// 3 us slower on 25088 -> 4096 at 12 frames, and would change the bits.
 void pick_fc_config(int64_t M, int64_t N, int64_t K, int &splits, int &kps) {
     // M: frames of the largest grid slice (a grouped launch takes the
     // configuration of one member's launch, so that its results are those
-    // of separate launches); N: neurons of the whole layer, also for a
-    // streamed block of its rows (the resident layer's results)
+    // of separate launches)
     const int64_t blocks = (N + 63) / 64;
-    const int64_t want = (256 + blocks - 1) / blocks;
-    const int64_t maxs = std::max<int64_t>(1, K / 512);
-    // frames staged in LDS (as the kernel computes them) and the depth that
-    // fits: kps * mp elements plus the last 64-slot run
-    const int64_t mp = M > 16 ? (M + 15) / 16 * 16 : M > 8 ? 16 : M > 4 ? 8 : M > 2 ? 4 : M;
-    const int64_t kps_cap = std::max<int64_t>(128, (fc_x_elems((int)((M + 15) / 16)) - 512) / mp / 128 * 128);
+    const int64_t want = (1024 + blocks - 1) / blocks;
+    const int64_t maxs = std::max<int64_t>(1, K / 1024);
+    // the depth that fits: kps * padded frames plus the last 64-slot run
+    const int64_t kps_cap = std::max<int64_t>(128, (FC_X_ELEMS / fc_slice_pad((int)M) - 64) / 128 * 128);
     splits = (int)std::max<int64_t>(1, std::min(want, maxs));
     splits = (int)std::max<int64_t>(splits, (K + kps_cap - 1) / kps_cap);
     kps = (int)round_up((K + splits - 1) / splits, 128);
@@ -1338,7 +1336,7 @@ static gemel_status build_plan(gemel_ctx *ctx, const std::vector<int> &ids, cons
                     }
                     Lc.kind = GEMEL_K_FC;
                     a.grouped = grouped ? 1 : 0;
-                    pick_fc_config(slice_frames, blob->rows, a.K, a.k_splits, a.k_per_split);
+                    pick_fc_config(slice_frames, a.N, a.K, a.k_splits, a.k_per_split);
                     Lc.type = L_FC_BF16;
                     if (a.k_splits > 1) {
                         step_partial[(size_t)step] = std::max(step_partial[(size_t)step], (size_t)a.k_splits * a.M * a.N * 4);

@@ -84,6 +84,15 @@ def main():
                                  [conv("c", -1, cin, cout, k, s_, p_, bn=True,
                                        act="leaky", out=True)], n, (cin, hw, hw))
                        for i, n in enumerate(frames)], [], "normal")
+    elif name == "fc":       # one FC layer (its consumer: a second, small one)
+        from workloads.configs import ModelSpec, Workload
+        sys.path.insert(0, os.path.join(ROOT, "tests"))
+        from test_gpu_layers import L as layer
+        k, n = kw["k"], kw["n"]
+        lay = [layer("f", "fc", -1, cin=k, cout=n, out=not kw.get("then"))]
+        if kw.get("then"):
+            lay.append(layer("g", "fc", 0, cin=n, cout=8, out=True))
+        wl = Workload("fc", 13, "bf16", [ModelSpec("m0", "custom", lay, kw["frames"], (k, 1, 1))], [], "normal")
     else:
         wl = configs.get(name, **kw)
     # the stub computes nothing: constant parameters of the right shapes

@@ -10,6 +10,7 @@ weight-swap schedule and split-K are all exercised. No GPU is needed."""
 
 import json
 import os
+import re
 import subprocess
 
 import pytest
@@ -43,7 +44,7 @@ def drive(lib, name, kw, opts, rounds=2, scenario=None):
                         json.dumps(scenario or {})],
                        capture_output=True, text=True, env=env, timeout=600)
     assert r.returncode == 0, r.stderr[-3000:]
-    return json.loads(r.stdout.strip().splitlines()[-1])
+    return dict(json.loads(r.stdout.strip().splitlines()[-1]), stderr=r.stderr)
 
 
 CASES = [
@@ -365,3 +366,35 @@ def test_profile_batches_runs_every_batch_and_frees_its_buffers(hostlib):
     assert out["status"] == [0, 0], out["error"]
     assert out["hazards"] == 0 and out["violations"] == 0, out["last"]
     assert out["leaked"] == 0
+
+
+def _fc_splits(hostlib, monkeypatch, k, n, frames, opts=None, **kw):
+    """(rows, splits) of each bf16 FC launch of one layer's round."""
+    monkeypatch.setenv("GEMEL_TRACE_PLAN", "1")
+    out = drive(hostlib, "fc", dict(kw, k=k, n=n, frames=frames), opts or {}, 1)
+    assert out["status"] == [0] and out["violations"] == 0 and out["hazards"] == 0, out["last"]
+    got = re.findall(r"plan \d+ fc_bf16 M=(\d+) N=(\d+) K=\d+ tile=\S+ splits=(\d+)", out["stderr"])
+    assert got
+    return [(int(r), int(sp)) for _, r, sp in got]
+
+
+# the splits fix the order of the float32 sums: about 1024 workgroups, splits
+# of at least 1024, the padded frames x depth of a split within 32768 - 64
+# elements a frame
+@pytest.mark.parametrize("k,n,frames,splits", [
+    (4096, 1000, 8, 4), (2048, 1000, 8, 2), (2048, 24, 1, 2), (512, 1000, 64, 2),
+    (25088, 640, 8, 22), (25088, 640, 12, 22), (25088, 640, 16, 22), (25088, 64, 32, 28),
+    (4096, 72, 16, 4), (4096, 72, 40, 8), (4096, 72, 64, 11), (31744, 8, 1, 31),
+])
+def test_fc_split_depths(hostlib, monkeypatch, k, n, frames, splits):
+    assert _fc_splits(hostlib, monkeypatch, k, n, frames) == [(n, splits)]
+
+
+def test_streamed_fc_blocks_split_by_their_own_rows(hostlib, monkeypatch):
+    """A block of a streamed FC layer's rows is split as a layer of that many
+    rows: blocks of 640 rows in 28, where the 2560 rows together take 25."""
+    k, n = 28672, 2560
+    opts = {"OPT_WEIGHT_BUDGET": 80 << 20, "OPT_SWAP_SLOT_BYTES": 640 * k * 2, "OPT_SWAP_SLOTS": 2}
+    got = _fc_splits(hostlib, monkeypatch, k, n, 8, opts, then=True)
+    assert got == [(640, 28)] * 4 + [(8, 2)]
+    assert _fc_splits(hostlib, monkeypatch, k, n, 8, then=True) == [(n, 25), (8, 2)]
