@@ -202,59 +202,104 @@ __global__ __launch_bounds__(256) void maxpool_kernel(const EwArgs a) {
     store8((T *)sg.out + ((size_t)f * items + idx) * 8, m);
 }
 
-// Global average pool: [f][H][W][C] -> [f][C], fp32 sums. Bound by the
-// latency of a thread's serial loads, so a workgroup takes CW = 4 or 16
-// 8-channel chunks of one frame and 256 / CW pixel groups, whose partial
-// sums meet in LDS (with 64 chunks and 4 groups, 16 x 16 x 32 float32 took
-// 17 us on one wave's lanes, 8 frames of 7 x 7 x 2048 bf16 6.9 us; here 2.6
-// and 4.7 us).
+// Global average pool: [f][H][W][C] -> [f][C], fp32 sums in one order whatever
+// the map's size and the launch: group g of 4 adds pixels g, g + 4, ... one
+// after the other, then the groups are added in order. Bound by the latency of
+// that chain's loads, so a workgroup takes CW = 4 or 16 8-channel chunks of one
+// frame and all its threads load a tile of 512 or 64 pixels into LDS, the next
+// tile in flight while a thread per group and channel pair adds (pixels beyond
+// the map are zeros: the sums are never -0, so adding 0 leaves them alone).
+// 8 frames of 7 x 7 x 2048 bf16 4.3 us, 16 x 16 x 32 float32 4.2, 48 x 48 x 32
+// bf16 9.8 (a wave's lanes loading as they add, in the same order: 6.1, 9.7 and
+// 146 us; 64 groups of pixels, in another: 4.4, 4.3 and 5.9).
 // Grid: x = frames * ceil(chunks / CW), y = segment.
 template <typename T, int CW>
 __global__ __launch_bounds__(256) void avgpool_kernel(const EwArgs a) {
-    constexpr int PG = 256 / CW;
-    __shared__ float part[PG][CW * 8 + 4];
+    constexpr int LP = 256 / CW, U = CW > 8 ? 4 : 8, P = LP * U;   // pixels of a load of the workgroup, and of a tile
+    constexpr int Q = (int)sizeof(T) / 2;             // 16-byte pieces of a chunk
+    constexpr int E = CW > 8 ? 2 : 1;                 // channels a thread adds
+    constexpr int AT = CW * 8 / E;                    // such threads per group
+    __shared__ uint4 tile[P * CW * Q];
+    __shared__ float part[4][CW * 8];
     const EwSeg &sg = a.seg[blockIdx.y];
     const int ch = a.C / 8, cblocks = (ch + CW - 1) / CW;
     const int f = (int)blockIdx.x / cblocks;
-    if (f >= sg.frames) return;
-    const int cl = threadIdx.x % CW, pg = threadIdx.x / CW;
-    const int c0 = ((int)blockIdx.x - f * cblocks) * CW, cc = c0 + cl;
+    if (f >= sg.frames) return;   // uniform: before the barriers
+    const int t = threadIdx.x;
+    const int cl = t % CW, pl = t / CW, c0 = ((int)blockIdx.x - f * cblocks) * CW;
+    const int c = t % AT, g = t / AT;
     const int hw = a.H * a.W;
-    float s[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-    if (cc < ch) {
-        const T *in = (const T *)sg.in0 + (size_t)f * hw * a.C + cc * 8;
-        int p = pg;
-        for (; p + 3 * PG < hw; p += 4 * PG) {
-            float v[4][8];
+    const T *in = (const T *)sg.in0 + (size_t)f * hw * a.C + min(c0 + cl, ch - 1) * 8;
+    uint4 v[U][Q];
+    auto load = [&](int p0) __attribute__((always_inline)) {
 #pragma unroll
-            for (int q = 0; q < 4; ++q) load8(in + (size_t)(p + q * PG) * a.C, v[q]);
+        for (int q = 0; q < U; ++q) {
+            const uint4 *src = (const uint4 *)(in + (size_t)min(p0 + q * LP + pl, hw - 1) * a.C);
 #pragma unroll
-            for (int q = 0; q < 4; ++q)
-#pragma unroll
-                for (int j = 0; j < 8; ++j) s[j] += v[q][j];
+            for (int i = 0; i < Q; ++i) v[q][i] = src[i];
         }
-        for (; p < hw; p += PG) {
-            float v[8];
-            load8(in + (size_t)p * a.C, v);
+    };
+    float s[E] = {};
+    // 16 pixels of this thread's group and channels, from pixel b of the tile
+    auto add16 = [&](int b) __attribute__((always_inline)) {
+        float x[16][E];
 #pragma unroll
-            for (int j = 0; j < 8; ++j) s[j] += v[j];
+        for (int i = 0; i < 16; ++i) {
+            const int at = (b + 4 * i + g) * AT + c;
+            if constexpr (sizeof(T) == 2 && E == 2) {
+                const uint32_t w = ((const uint32_t *)tile)[at];
+                x[i][0] = __uint_as_float(w << 16);
+                x[i][1] = __uint_as_float(w & 0xffff0000u);
+            } else if constexpr (E == 2) {
+                const float2 w = ((const float2 *)tile)[at];
+                x[i][0] = w.x;
+                x[i][1] = w.y;
+            } else if constexpr (sizeof(T) == 2) {
+                x[i][0] = m_bf2f(((const u16 *)tile)[at]);
+            } else {
+                x[i][0] = ((const float *)tile)[at];
+            }
+        }
+#pragma unroll
+        for (int i = 0; i < 16; ++i)
+#pragma unroll
+            for (int e = 0; e < E; ++e) s[e] += x[i][e];
+    };
+    load(0);
+    for (int p0 = 0; p0 < hw; p0 += P) {
+        if (p0) __syncthreads();   // the tile before has been added
+#pragma unroll
+        for (int q = 0; q < U; ++q) {
+            const bool ok = p0 + q * LP + pl < hw;
+#pragma unroll
+            for (int i = 0; i < Q; ++i)
+                tile[((q * LP + pl) * CW + cl) * Q + i] = ok ? v[q][i] : make_uint4(0, 0, 0, 0);
+        }
+        __syncthreads();
+        if (p0 + P < hw) load(p0 + P);
+        if (g < 4) {
+            if constexpr (P == 64) {
+                add16(0);
+            } else if (p0 + P <= hw) {
+#pragma unroll
+                for (int b = 0; b < P; b += 64) add16(b);
+            } else {
+                for (int b = 0; b < hw - p0; b += 64) add16(b);
+            }
         }
     }
+    if (g < 4) {
 #pragma unroll
-    for (int j = 0; j < 8; ++j) part[pg][cl * 8 + j] = s[j];
+        for (int e = 0; e < E; ++e) part[g][c * E + e] = s[e];
+    }
     __syncthreads();
-    // one thread per channel sums the groups, in order
-    const int c = threadIdx.x;
-    if (c < CW * 8 && c0 * 8 + c < a.C) {
-        float t = 0.f;
-#pragma unroll 16
-        for (int q = 0; q < PG; ++q) t += part[q][c];
-        t *= 1.0f / (float)hw;
-        T *o = (T *)sg.out + (size_t)f * a.C + c0 * 8 + c;
+    if (t < CW * 8 && c0 * 8 + t < a.C) {
+        const float m = (part[0][t] + part[1][t] + part[2][t] + part[3][t]) * (1.0f / (float)hw);
+        T *o = (T *)sg.out + (size_t)f * a.C + c0 * 8 + t;
         if constexpr (sizeof(T) == 2)
-            *o = m_f2bf(t);
+            *o = m_f2bf(m);
         else
-            *o = t;
+            *o = m;
     }
 }
 

@@ -7,6 +7,7 @@ float32 (a bf16 rounding, or (pixels + 2) * 2^-24 of the mean magnitude)."""
 
 import numpy as np
 import pytest
+import torch
 
 from harness import GpuWorkload
 from test_gpu_layers import L
@@ -68,6 +69,25 @@ def test_average_pool(c, hw, dtype):
         if dtype == "bf16":
             bound = bound + 2.0 ** -8 * (np.abs(ref) + bound)
         assert np.all(np.abs(outs[0] - ref) <= bound)
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("c,hw", [(8, (1, 1)), (24, (1, 3)), (32, (16, 16)), (32, (17, 15)), (32, (37, 29)), (40, (7, 7)),
+                                  (136, (8, 8)), (136, (5, 13)), (136, (3, 50)), (2048, (7, 7))])
+def test_average_pool_order_of_sums(c, hw, dtype):
+    """Group g of 4 adds pixels g, g + 4, ... one after the other in float32,
+    then the groups are added in order: the result is exact to the bit."""
+    fr, got = run([L("a", "avgpool", -1, cin=c, cout=c, out=True)], (c,) + hw, [2, 5], dtype)
+    n = np.float32(hw[0] * hw[1])
+    for x, outs in zip(fr, got):
+        px = x.reshape(x.shape[0], c, -1)
+        part = [np.zeros(px.shape[:2], np.float32) for _ in range(4)]
+        for p in range(px.shape[2]):
+            part[p % 4] = part[p % 4] + px[:, :, p]
+        ref = (((part[0] + part[1]) + part[2]) + part[3]) * (np.float32(1) / n)
+        if dtype == "bf16":
+            ref = torch.from_numpy(ref).bfloat16().float().numpy()
+        assert np.array_equal(outs[0].reshape(ref.shape), ref)
 
 
 @pytest.mark.parametrize("models", [2, 18], ids=["two", "more-than-a-launch-holds"])
