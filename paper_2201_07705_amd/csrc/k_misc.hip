@@ -4,6 +4,8 @@
 // covers all models of a node, blockIdx.y selecting the model's segment.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
+
 #include "kargs.h"
 #include "kernels.h"
 
@@ -43,6 +45,10 @@ __device__ __forceinline__ void copy8(float *d, const float *s) {
     *(float4 *)(d + 4) = *(const float4 *)(s + 4);
 }
 
+// This workgroup's number in its segment: x and z of the grid together, as a
+// launch holds fewer than 2^32 threads along x (frame_launch).
+__device__ __forceinline__ uint32_t wg_number() { return blockIdx.z * gridDim.x + blockIdx.x; }
+
 // Caller frames NCHW f32 -> NHWC, channels zero-padded to Co, for images
 // (Co = 8): bound by HBM latency and bytes (12 or 16 read for 16 or 32
 // written a pixel), so a thread has the loads of PX pixels in flight, 256
@@ -50,25 +56,27 @@ __device__ __forceinline__ void copy8(float *d, const float *s) {
 // count, or 8 for any (up to 8, those beyond it read again and dropped). The
 // loads are unconditional, at clamped addresses: a load inside a branch is
 // waited for at the branch's end.
-// Grid: x = frames * ceil(hw / (256 * PX)), y = segment.
+// Grid: x, z = frames * ceil(hw / (256 * PX)), y = segment.
 template <typename T, int PX, int CL>
 __global__ __launch_bounds__(256) void pack_image_kernel(const EwArgs a) {
     const EwSeg &sg = a.seg[blockIdx.y];
-    const int hw = a.H * a.W, per = (hw + 256 * PX - 1) / (256 * PX);
-    const int f = (int)blockIdx.x / per, p0 = ((int)blockIdx.x - f * per) * 256 * PX + (int)threadIdx.x;
+    const long hw = (long)a.H * a.W;
+    const uint32_t wg = wg_number(), per = (uint32_t)((hw + 256 * PX - 1) / (256 * PX));
+    const int f = (int)(wg / per);
+    const long p0 = (long)(wg - f * per) * 256 * PX + threadIdx.x;
     if (f >= sg.frames) return;
     const float *src = (const float *)sg.in0 + (size_t)f * a.c_logical * hw;
     T *dst = (T *)sg.out + (size_t)f * hw * 8;
     float v[PX][8];
 #pragma unroll
     for (int q = 0; q < PX; ++q) {
-        const int p = min(p0 + q * 256, hw - 1);
+        const long p = min(p0 + q * 256, hw - 1);
 #pragma unroll
         for (int j = 0; j < CL; ++j) v[q][j] = src[(size_t)(CL == 8 ? min(j, a.c_logical - 1) : j) * hw + p];
     }
 #pragma unroll
     for (int q = 0; q < PX; ++q) {
-        const int p = p0 + q * 256;
+        const long p = p0 + q * 256;
 #pragma unroll
         for (int j = 0; j < 8; ++j) v[q][j] = j < CL && j < a.c_logical ? v[q][j] : 0.f;
         if (p < hw) store8(dst + (size_t)p * 8, v[q]);
@@ -108,15 +116,17 @@ struct TransTile {
 // per pixel walking all channels (the form before) left the chip idle: 8
 // frames of 1024 x 14 x 14 took 286 us on 8 workgroups, 4.4 us here; 16
 // frames of 256 x 56 x 56 72 us, 14 us here (5.5 TB/s).
-// Grid: x = frames * ceil(hw / 64) * ceil(Co / 64), y = segment.
+// Grid: x, z = frames * ceil(hw / 64) * ceil(Co / 64), y = segment.
 template <typename T>
 __global__ __launch_bounds__(256) void pack_tile_kernel(const EwArgs a) {
     using TT = TransTile<T>;
     __shared__ uint4 lds[64 * TT::CH];
     const EwSeg &sg = a.seg[blockIdx.y];
-    const int hw = a.H * a.W, per = (hw + 63) / 64, cb = (a.Co + 63) / 64;
-    const int tile = (int)blockIdx.x / cb, c0 = ((int)blockIdx.x - tile * cb) * 64;
-    const int f = tile / per, p0 = (tile - f * per) * 64;
+    const long hw = (long)a.H * a.W;
+    const uint32_t wg = wg_number(), per = (uint32_t)((hw + 63) / 64), cb = (uint32_t)(a.Co + 63) / 64;
+    const uint32_t tile = wg / cb;
+    const int c0 = (int)(wg - tile * cb) * 64, f = (int)(tile / per);
+    const long p0 = (long)(tile - f * per) * 64;
     if (f >= sg.frames) return;   // uniform: before the barrier
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const float *src = (const float *)sg.in0 + (size_t)f * a.c_logical * hw + min(p0 + lane, hw - 1);
@@ -140,13 +150,13 @@ __global__ __launch_bounds__(256) void pack_tile_kernel(const EwArgs a) {
     }
 }
 
-// Grid of ceil(items / 256) workgroups per frame: this thread's frame and
-// its item of the frame (32-bit divisions, the frame's by scalars). False
-// for threads beyond either.
+// Grid of ceil(items / 256) workgroups per frame (items up to 2^32 - 256):
+// this thread's frame and its item of the frame (32-bit divisions, the
+// frame's by scalars). False for threads beyond either.
 __device__ __forceinline__ bool frame_item(uint32_t items, int frames, uint32_t &f, uint32_t &idx) {
-    const uint32_t per = (items + 255) / 256;
-    f = blockIdx.x / per;
-    idx = (blockIdx.x - f * per) * 256 + threadIdx.x;
+    const uint32_t wg = wg_number(), per = (items + 255) / 256;
+    f = wg / per;
+    idx = (wg - f * per) * 256 + threadIdx.x;
     return (int)f < frames && idx < items;
 }
 
@@ -170,11 +180,11 @@ __global__ __launch_bounds__(256) void maxpool_kernel(const EwArgs a) {
     for (int j = 0; j < 8; ++j) m[j] = -INFINITY;
     if constexpr (K > 0) {
         const T *p[K];
-        int wi[K];
+        size_t wi[K];
 #pragma unroll
         for (int i = 0; i < K; ++i) {
             p[i] = in + (size_t)min(max(h0 + i, 0), a.H - 1) * a.W * a.C;
-            wi[i] = min(max(w0 + i, 0), a.W - 1) * a.C;
+            wi[i] = (size_t)min(max(w0 + i, 0), a.W - 1) * a.C;
         }
 #pragma unroll
         for (int i = 0; i < K; ++i)
@@ -212,7 +222,7 @@ __global__ __launch_bounds__(256) void maxpool_kernel(const EwArgs a) {
 // 8 frames of 7 x 7 x 2048 bf16 4.3 us, 16 x 16 x 32 float32 4.2, 48 x 48 x 32
 // bf16 9.8 (a wave's lanes loading as they add, in the same order: 6.1, 9.7 and
 // 146 us; 64 groups of pixels, in another: 4.4, 4.3 and 5.9).
-// Grid: x = frames * ceil(chunks / CW), y = segment.
+// Grid: x, z = frames * ceil(chunks / CW), y = segment.
 template <typename T, int CW>
 __global__ __launch_bounds__(256) void avgpool_kernel(const EwArgs a) {
     constexpr int LP = 256 / CW, U = CW > 8 ? 4 : 8, P = LP * U;   // pixels of a load of the workgroup, and of a tile
@@ -223,15 +233,15 @@ __global__ __launch_bounds__(256) void avgpool_kernel(const EwArgs a) {
     __shared__ float part[4][CW * 8];
     const EwSeg &sg = a.seg[blockIdx.y];
     const int ch = a.C / 8, cblocks = (ch + CW - 1) / CW;
-    const int f = (int)blockIdx.x / cblocks;
+    const int wg = (int)wg_number(), f = wg / cblocks;
     if (f >= sg.frames) return;   // uniform: before the barriers
     const int t = threadIdx.x;
-    const int cl = t % CW, pl = t / CW, c0 = ((int)blockIdx.x - f * cblocks) * CW;
+    const int cl = t % CW, pl = t / CW, c0 = (wg - f * cblocks) * CW;
     const int c = t % AT, g = t / AT;
-    const int hw = a.H * a.W;
+    const long hw = (long)a.H * a.W;
     const T *in = (const T *)sg.in0 + (size_t)f * hw * a.C + min(c0 + cl, ch - 1) * 8;
     uint4 v[U][Q];
-    auto load = [&](int p0) __attribute__((always_inline)) {
+    auto load = [&](long p0) __attribute__((always_inline)) {
 #pragma unroll
         for (int q = 0; q < U; ++q) {
             const uint4 *src = (const uint4 *)(in + (size_t)min(p0 + q * LP + pl, hw - 1) * a.C);
@@ -266,7 +276,7 @@ __global__ __launch_bounds__(256) void avgpool_kernel(const EwArgs a) {
             for (int e = 0; e < E; ++e) s[e] += x[i][e];
     };
     load(0);
-    for (int p0 = 0; p0 < hw; p0 += P) {
+    for (long p0 = 0; p0 < hw; p0 += P) {
         if (p0) __syncthreads();   // the tile before has been added
 #pragma unroll
         for (int q = 0; q < U; ++q) {
@@ -335,21 +345,23 @@ __global__ __launch_bounds__(256) void concat_kernel(const EwArgs a) {
 // pixel, writes 256 bytes of one channel plane per wave (8 x 64 x 56 x 56
 // from bf16: 5.0 us; a thread per pixel and 8 channels, reading 16 bytes of
 // each line, 6.1 us).
-// Grid: x = frames * ceil(hw / 64) * ceil(c_logical / 64), y = segment.
+// Grid: x, z = frames * ceil(hw / 64) * ceil(c_logical / 64), y = segment.
 template <typename T>
 __global__ __launch_bounds__(256) void export_kernel(const EwArgs a) {
     using TT = TransTile<T>;
     __shared__ uint4 lds[64 * TT::CH];
     const EwSeg &sg = a.seg[blockIdx.y];
-    const int hw = a.H * a.W, per = (hw + 63) / 64, cb = (a.c_logical + 63) / 64;
-    const int tile = (int)blockIdx.x / cb, c0 = ((int)blockIdx.x - tile * cb) * 64;
-    const int f = tile / per, p0 = (tile - f * per) * 64;
+    const long hw = (long)a.H * a.W;
+    const uint32_t wg = wg_number(), per = (uint32_t)((hw + 63) / 64), cb = (uint32_t)(a.c_logical + 63) / 64;
+    const uint32_t tile = wg / cb;
+    const int c0 = (int)(wg - tile * cb) * 64, f = (int)(tile / per);
+    const long p0 = (long)(tile - f * per) * 64;
     if (f >= sg.frames) return;   // uniform: before the barrier
     const int ch = threadIdx.x % TT::CH, px0 = threadIdx.x / TT::CH;
     const T *src = (const T *)sg.in0 + ((size_t)f * hw + p0) * a.C + min(c0 + ch * TT::EPC, a.C - TT::EPC);
     uint4 x[64 / TT::RPI];
 #pragma unroll
-    for (int q = 0; q < 64 / TT::RPI; ++q) x[q] = *(const uint4 *)(src + (size_t)min(px0 + q * TT::RPI, hw - 1 - p0) * a.C);
+    for (int q = 0; q < 64 / TT::RPI; ++q) x[q] = *(const uint4 *)(src + (size_t)min((long)(px0 + q * TT::RPI), hw - 1 - p0) * a.C);
 #pragma unroll
     for (int q = 0; q < 64 / TT::RPI; ++q) lds[TT::slot(px0 + q * TT::RPI, ch)] = x[q];
     __syncthreads();
@@ -389,16 +401,17 @@ static bool ew_ok(const EwArgs &a, bool need_in1) {
     return true;
 }
 
-// A grid of `blocks` workgroups per frame in x, one segment in y.
+// A grid of `blocks` workgroups per frame in x, one segment in y; more than
+// 2^23 of them (2^31 threads) go on in z.
 static hipError_t frame_launch(const void *kern, long blocks, const EwArgs &a, const Sink &sk) {
-    const long n = blocks * a.max_frames;
+    if (blocks > 0x7fffffffL || blocks * a.max_frames > 0x7fffffffL) return hipErrorInvalidValue;
+    const long n = blocks * a.max_frames, x = std::min(n, 1L << 23);
     if (n <= 0) return submit_nothing(sk);
-    if (n > 0x7fffffffL) return hipErrorInvalidValue;
-    return submit(sk, kern, dim3((unsigned)n, (unsigned)a.nseg), dim3(256), a);
+    return submit(sk, kern, dim3((unsigned)x, (unsigned)a.nseg, (unsigned)((n + x - 1) / x)), dim3(256), a);
 }
 // One thread per item of a frame (frame_item).
 static hipError_t item_launch(const void *kern, long items, const EwArgs &a, const Sink &sk) {
-    return items > 0x7fffff00L ? hipErrorInvalidValue : frame_launch(kern, (items + 255) / 256, a, sk);
+    return items > 0xffffff00L ? hipErrorInvalidValue : frame_launch(kern, (items + 255) / 256, a, sk);
 }
 
 template <typename T, int PX>
@@ -411,7 +424,6 @@ static const void *pack_image_of(int c) {
 hipError_t launch_pack(const EwArgs &a, bool bf16, const Sink &sk) {
     if (!ew_ok(a, false) || a.Co % 8 || a.c_logical > a.Co || a.c_logical <= 0) return hipErrorInvalidValue;
     const long hw = (long)a.H * a.W;
-    if (hw > 0x3fffffffL) return hipErrorInvalidValue;
     if (a.Co == 8) {
         // 4 pixels a thread where that still leaves four workgroups per CU
         const bool wide = (hw + 1023) / 1024 * a.max_frames * a.nseg >= 1024;
@@ -441,7 +453,7 @@ hipError_t launch_maxpool(const EwArgs &a, bool bf16, const Sink &sk) {
 }
 
 hipError_t launch_avgpool(const EwArgs &a, bool bf16, const Sink &sk) {
-    if (!ew_ok(a, false) || a.C % 8 || a.H <= 0 || a.W <= 0 || (long)a.H * a.W > 0x3fffffffL) return hipErrorInvalidValue;
+    if (!ew_ok(a, false) || a.C % 8 || a.H <= 0 || a.W <= 0) return hipErrorInvalidValue;
     const int cw = a.C / 8 <= 4 ? 4 : 16;
     const void *k = cw == 4 ? (bf16 ? reinterpret_cast<const void *>(&avgpool_kernel<u16, 4>)
                                     : reinterpret_cast<const void *>(&avgpool_kernel<float, 4>))
@@ -467,7 +479,6 @@ hipError_t launch_concat(const EwArgs &a, bool bf16, const Sink &sk) {
 hipError_t launch_export(const EwArgs &a, bool bf16, const Sink &sk) {
     if (!ew_ok(a, false) || a.C % 8 || a.c_logical > a.C || a.c_logical <= 0) return hipErrorInvalidValue;
     const long hw = (long)a.H * a.W;
-    if (hw > 0x3fffffffL) return hipErrorInvalidValue;
     const void *k = bf16 ? reinterpret_cast<const void *>(&export_kernel<u16>)
                          : reinterpret_cast<const void *>(&export_kernel<float>);
     return frame_launch(k, (hw + 63) / 64 * ((a.c_logical + 63) / 64), a, sk);

@@ -118,3 +118,49 @@ def test_pooling_and_routing_of_several_models_share_launches(models):
     packs = (models + 15) // 16
     assert launches[1] == packs + 7 * models
     assert launches[0] == packs + 7 * packs
+
+
+def _large(layers, chw):
+    """One frame of bf16 values on the device and its outputs."""
+    import paper_2201_07705_amd as P
+    print("large map", chw, flush=True)
+    ctx = P.Context(0, "bf16")
+    try:
+        i = ctx.register_model(layers, [None] * len(layers), chw)
+        x = torch.randint(-127, 128, (1,) + chw, dtype=torch.int8, device="cuda",
+                          generator=torch.Generator("cuda").manual_seed(5)).float()
+        s = torch.cuda.Stream()
+        s.wait_stream(torch.cuda.current_stream())
+        outs = ctx.infer([i], [x], stream=s)[0]
+        s.synchronize()
+        return x, outs
+    finally:
+        ctx.close()
+
+
+@pytest.mark.parametrize("times", [1, 2])
+def test_maps_of_2_30_pixels_and_2_31_items(times):
+    """The largest frames upsampled: a map of 2^30 pixels pooled, averaged and
+    exported, and one of 2^31 8-channel items exported."""
+    torch.cuda.empty_cache()
+    h, w = (16384, 16384) if times == 1 else (8192, 16384)
+    lay = [L("u", "upsample", -1, cin=1, cout=1, out=True)]
+    if times == 1:
+        lay += [L("p", "maxpool", 0, cin=1, cout=1, kh=2, kw=2, stride=2, out=True),
+                L("a", "avgpool", 0, cin=1, cout=1, out=True)]
+    else:
+        lay = [L("u0", "upsample", -1, cin=1, cout=1), L("u", "upsample", 0, cin=1, cout=1, out=True)]
+    x, outs = _large(lay, (1, h, w))
+    k = 2 * times
+    up = outs[0].view(h, k, w, k)
+    for dy in range(k):
+        for dx in range(k):
+            assert torch.equal(up[:, dy, :, dx], x[0, 0])
+    if times == 1:
+        assert torch.equal(outs[1], x)
+        # symmetric whole numbers: sums of 2^28 of them wander by about 2^20,
+        # well within the 2^24 up to which float32 sums are exact
+        mean = x.sum(dtype=torch.float64) / 2 ** 28
+        assert float(outs[2]) == float(mean.float().bfloat16())
+    del x, outs, up
+    torch.cuda.empty_cache()
