@@ -84,6 +84,10 @@ def main():
                                  [conv("c", -1, cin, cout, k, s_, p_, bn=True,
                                        act="leaky", out=True)], n, (cin, hw, hw))
                        for i, n in enumerate(frames)], [], "normal")
+    elif name == "cycle":    # shared convs in opposite order (tests/test_gpu_layout.py)
+        sys.path.insert(0, os.path.join(ROOT, "tests"))
+        from test_gpu_layout import cycle_workload
+        wl = cycle_workload()
     elif name == "fc":       # one FC layer (its consumer: a second, small one)
         from workloads.configs import ModelSpec, Workload
         sys.path.insert(0, os.path.join(ROOT, "tests"))

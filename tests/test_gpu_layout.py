@@ -9,7 +9,7 @@ import numpy as np
 import pytest
 import torch
 
-from harness import GpuWorkload
+from harness import GpuWorkload, compare, oracle_outputs
 from test_gpu_layers import L
 from workloads.configs import ModelSpec, Workload
 
@@ -118,6 +118,62 @@ def test_pooling_and_routing_of_several_models_share_launches(models):
     packs = (models + 15) // 16
     assert launches[1] == packs + 7 * models
     assert launches[0] == packs + 7 * packs
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+def test_max_pool_of_nan_and_infinities(dtype):
+    """Out-of-range taps count as -Inf and NaN never wins: windows of -Inf or
+    NaN alone give -Inf, at the border and inside, at each window size."""
+    c, h, w = 8, 9, 7
+    lay = [L(f"p{k}", "maxpool", -1, cin=c, cout=c, kh=k, kw=k, stride=s, pad=p, out=True)
+           for k, s, p in ((2, 1, 1), (2, 2, 0), (3, 2, 1), (3, 1, 1), (5, 2, 2))]
+    wl = Workload("nan", 19, dtype, [ModelSpec("m", "custom", lay, 2, (c, h, w))], [], "normal")
+    x = wl.frames(0)
+    x[:, 0] = -np.inf
+    x[:, 1, 2:7, 1:6] = np.nan
+    x[:, 2] = np.nan
+    x[:, 3, ::2] = -np.inf
+    x[:, 3, 1, 1] = np.nan
+    x[:, 4, 3, 3] = np.inf
+    g = GpuWorkload(wl)
+    try:
+        outs = g.run([x])[0]
+    finally:
+        g.close()
+    for l, o in zip(lay, outs):
+        k, p = l["kh"], l["pad"]
+        z = np.pad(np.where(np.isnan(x), -np.inf, x), ((0, 0), (0, 0), (p, p), (p, p)), constant_values=-np.inf)
+        v = np.lib.stride_tricks.sliding_window_view(z, (k, k), axis=(2, 3))
+        assert np.array_equal(o, v[:, :, ::l["stride"], ::l["stride"]].max((4, 5)))
+
+
+def cycle_workload(dtype="bf16"):
+    """Two models that share two convs and run them in opposite order, with a
+    pool behind the same one in both: launches that take both models' convs
+    would wait for each other."""
+    def conv(name, src, **kw):
+        return L(name, "conv", src, cin=16, cout=16, kh=3, kw=3, pad=1, bias=True, act="relu", **kw)
+
+    def pool(src, **kw):
+        return L("p", "maxpool", src, cin=16, cout=16, kh=3, kw=3, stride=1, pad=1, **kw)
+
+    a = [conv("x", -1), pool(0), conv("y", 1), pool(2, out=True)]
+    b = [conv("y", -1), conv("x", 0), pool(1), pool(2, out=True)]
+    ms = [ModelSpec("a", "custom", a, 2, (16, 12, 12)), ModelSpec("b", "custom", b, 3, (16, 12, 12))]
+    return Workload("cycle", 43, dtype, ms, [[(0, 0), (1, 1)], [(0, 2), (1, 0)]], "normal")
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+def test_pool_behind_convs_shared_in_opposite_order(dtype):
+    wl = cycle_workload(dtype)
+    params = [wl.params(i) for i in range(2)]
+    fr = [wl.frames(i) for i in range(2)]
+    g = GpuWorkload(wl, params)
+    try:
+        got = g.run(fr, repeat=3)
+    finally:
+        g.close()
+    compare(wl, got, oracle_outputs(wl, params, fr), tag=f"cycle-{dtype}", check_argmax=False)
 
 
 def _large(layers, chw):

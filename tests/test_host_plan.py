@@ -368,6 +368,18 @@ def test_profile_batches_runs_every_batch_and_frees_its_buffers(hostlib):
     assert out["leaked"] == 0
 
 
+@pytest.mark.parametrize("opts", [{}, {"OPT_STREAMS": 8, "OPT_FORK_US": 0}, {"OPT_GROUP_UNMERGED": 0}])
+def test_pool_behind_convs_shared_in_opposite_order(hostlib, opts):
+    """Two models that run their shared convs in opposite order, with the same
+    pool behind one of them: the launches on the cycle run per model, in
+    bounds and ordered."""
+    out = drive(hostlib, "cycle", {}, opts, 3)
+    assert out["status"] == [0] * 3, out["error"]
+    assert out["hazards"] == 0 and out["violations"] == 0, out["last"]
+    # one pack; per model two convs, two pools and an export
+    assert out["plan_launches"] == 1 + 4 + 4 + 2
+
+
 def _fc_splits(hostlib, monkeypatch, k, n, frames, opts=None, **kw):
     """(rows, splits) of each bf16 FC launch of one layer's round."""
     monkeypatch.setenv("GEMEL_TRACE_PLAN", "1")
