@@ -2,10 +2,11 @@
 //
 // Same GEMM as conv_bf16 (C[M][N] = A[M][K] * B[N][K]^T over the merged
 // frames of several models, bf16 MFMA, fp32 accumulation, fused epilogue),
-// organised for latency tolerance: each depth step of 32 is fetched by
+// organised for latency tolerance: each depth step of 32 or 64 is fetched by
 // global_load_lds_dwordx4 straight into one of STAGES LDS buffers, so
-// STAGES-1 steps are in flight while the MFMAs consume the oldest one and
-// no registers hold staged data. Each stage lives in its own __shared__
+// STAGES-1 steps are in flight while the MFMAs consume the oldest one (all
+// STAGES where a step's fragments wait in registers) and no registers hold
+// staged data. Each stage lives in its own __shared__
 // array (the compiler then tracks which buffer an outstanding LDS-DMA
 // writes and waits only where a read could alias it); the waits on the
 // loads are explicit vmcnt counts, and workgroup syncs are bare s_barrier
@@ -232,6 +233,7 @@ __global__ __launch_bounds__(64 * WM *WN, (dma_min_waves<BM, BN, WM, WN, STAGES,
     // with segments of different sizes, each row takes its segment's sizes
     // (and its frame within the segment from the rows before it)
     constexpr bool hetero = MODE == 2;
+    static_assert(!PHASED || !hetero, "the phased loop walks one map size");
     const int Wp = a.Wo >> 1, HWp = HWo >> 2;
     const u16 *abase[AI];
     int ahi[AI], awi[AI], acq[AI];
@@ -313,8 +315,7 @@ __global__ __launch_bounds__(64 * WM *WN, (dma_min_waves<BM, BN, WM, WN, STAGES,
     if constexpr (PHASED) {
 #pragma unroll
         for (int i = 0; i < AI; ++i)
-            arow[i] = abase[i] + ((ptrdiff_t)(ahi[i] + lr) * (hetero ? aW[hetero ? i : 0] : W) + awi[i] + ls) * in_cs +
-                      acq[i] * 8;
+            arow[i] = abase[i] + ((ptrdiff_t)(ahi[i] + lr) * W + awi[i] + ls) * in_cs + acq[i] * 8;
     }
     auto set_tap = [&]() __attribute__((always_inline)) {
         if constexpr (PHASED) inside = 0;
@@ -344,8 +345,7 @@ __global__ __launch_bounds__(64 * WM *WN, (dma_min_waves<BM, BN, WM, WN, STAGES,
             const bool wrap = ++ls == kw;
             if constexpr (PHASED) {
 #pragma unroll
-                for (int i = 0; i < AI; ++i)
-                    arow[i] += wrap ? ((hetero ? aW[hetero ? i : 0] : W) - (kw - 1)) * in_cs : in_cs;
+                for (int i = 0; i < AI; ++i) arow[i] += wrap ? (W - (kw - 1)) * in_cs : in_cs;
             }
             if (wrap) { ls = 0; ++lr; }
             set_tap();

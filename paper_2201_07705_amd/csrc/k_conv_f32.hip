@@ -294,7 +294,12 @@ static hipError_t launch_f32(const ConvArgs &a, const Sink &sk) {
                      : kw == 2 ? reinterpret_cast<const void *>(&conv_f32_mfma_kernel<FM, FN, 2, 2>)
                      : kw == 4 ? reinterpret_cast<const void *>(&conv_f32_mfma_kernel<FM, FN, 4, 1>)
                      : kw == 8 ? reinterpret_cast<const void *>(&conv_f32_mfma_kernel<FM, FN, 8, 1>)
-                               : reinterpret_cast<const void *>(&conv_f32_mfma_kernel<FM, FN, 16, 1>);
+                               : nullptr;
+    // (2 x 2 fragments come in 256 tiles or more: at most 8 waves)
+    if constexpr (FM * FN < 4) {
+        if (kw == 16) fn = reinterpret_cast<const void *>(&conv_f32_mfma_kernel<FM, FN, 16, 1>);
+    }
+    if (!fn) return hipErrorInvalidValue;
     return submit(sk, fn, dim3((unsigned)blocks), dim3(64 * kw * mw), a);
 }
 

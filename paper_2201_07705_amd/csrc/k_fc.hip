@@ -67,15 +67,12 @@ __device__ __forceinline__ FcRow fc_row(const FcArgs &a, int f) {
     return r;
 }
 
-__device__ __forceinline__ void fc_store(const FcArgs &a, int f, int n, float acc, bool bf16) {
+__device__ __forceinline__ void fc_store(const FcArgs &a, int f, int n, float acc) {
     const FcRow sg = fc_row(a, f);
     const int lf = f - sg.f_start;
     const float y = fc_act(acc * sg.scale[n] + sg.shift[n], a.act, a.slope);
     if (a.out_mode == OUT_NHWC) {
-        if (bf16)
-            ((u16 *)sg.out)[(size_t)lf * a.out_cs + n] = fc_f2bf(y);
-        else
-            ((float *)sg.out)[(size_t)lf * a.out_cs + n] = y;
+        ((u16 *)sg.out)[(size_t)lf * a.out_cs + n] = fc_f2bf(y);
     } else if (n < a.cout) {
         ((float *)sg.out)[(size_t)lf * a.cout + n] = y;
     }
@@ -245,7 +242,7 @@ __global__ __launch_bounds__(256) void fc_bf16_kernel(const FcArgs a) {
             if (a.k_splits > 1)
                 store_partial1(a.partial + ((size_t)blockIdx.y * a.M + f) * a.N + n, acc[mb][v]);
             else
-                fc_store(a, f, n, acc[mb][v], true);
+                fc_store(a, f, n, acc[mb][v]);
         }
     }
     // fused split-K reduction: the last split of this column of neurons
@@ -282,19 +279,18 @@ __global__ __launch_bounds__(256) void fc_bf16_kernel(const FcArgs a) {
             }
 #pragma unroll
             for (int u = 0; u < 2; ++u)
-                if (i0 + u * 256 < mz * COLS && n[u] < a.N) fc_store(a, f[u], n[u], sum[u], true);
+                if (i0 + u * 256 < mz * COLS && n[u] < a.N) fc_store(a, f[u], n[u], sum[u]);
         }
     }
 }
 
-template <bool BF16>
 __global__ __launch_bounds__(256) void fc_reduce_kernel(const FcArgs a) {
     const long idx = (long)blockIdx.x * 256 + threadIdx.x;
     if (idx >= (long)a.M * a.N) return;
     const int f = (int)(idx / a.N), n = (int)(idx - (long)f * a.N);
     float acc = 0.f;
     for (int s = 0; s < a.k_splits; ++s) acc += a.partial[((size_t)s * a.M + f) * a.N + n];
-    fc_store(a, f, n, acc, BF16);
+    fc_store(a, f, n, acc);
 }
 
 static bool fc_args_ok(const FcArgs &a) {
@@ -338,12 +334,11 @@ hipError_t launch_fc_bf16(const FcArgs &a, const Sink &sk) {
     return submit(sk, fn, grid, block, a);
 }
 
-hipError_t launch_fc_reduce(const FcArgs &a, bool bf16, const Sink &sk) {
+hipError_t launch_fc_reduce(const FcArgs &a, const Sink &sk) {
     if (!fc_args_ok(a) || a.k_splits < 2) return hipErrorInvalidValue;
     const long n = (long)a.M * a.N;
     dim3 grid((unsigned)((n + 255) / 256)), block(256);
-    return bf16 ? submit(sk, reinterpret_cast<const void *>(&fc_reduce_kernel<true>), grid, block, a)
-                : submit(sk, reinterpret_cast<const void *>(&fc_reduce_kernel<false>), grid, block, a);
+    return submit(sk, reinterpret_cast<const void *>(&fc_reduce_kernel), grid, block, a);
 }
 
 }  // namespace gemel

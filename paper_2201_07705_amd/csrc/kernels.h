@@ -137,7 +137,7 @@ inline int64_t fc_slice_elems(int frames, int64_t depth) {
     return (depth / 8 * fc_slice_pad(frames) + 63) / 64 * 64 * 8;
 }
 hipError_t launch_fc_bf16(const FcArgs &a, const Sink &sk);
-hipError_t launch_fc_reduce(const FcArgs &a, bool bf16, const Sink &sk);
+hipError_t launch_fc_reduce(const FcArgs &a, const Sink &sk);
 
 // Input pack: caller NCHW f32 -> NHWC physical channels (bf16 or f32).
 hipError_t launch_pack(const EwArgs &a, bool bf16, const Sink &sk);

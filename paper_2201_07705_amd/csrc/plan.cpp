@@ -1708,7 +1708,7 @@ hipError_t launch_one(Launch &L, const CallPtrs &cp, const Plan &P, void *wptr, 
     case L_CONV_F32: return launch_conv_f32(L.conv, st);
     case L_CONV_REDUCE: return launch_conv_reduce(L.red, L.bf16, st);
     case L_FC_BF16: return launch_fc_bf16(L.fc, st);
-    case L_FC_REDUCE: return launch_fc_reduce(L.fc, L.bf16, st);
+    case L_FC_REDUCE: return launch_fc_reduce(L.fc, st);
     case L_MAXPOOL: return launch_maxpool(L.ew, L.bf16, st);
     case L_AVGPOOL: return launch_avgpool(L.ew, L.bf16, st);
     case L_UPSAMPLE: return launch_upsample2x(L.ew, L.bf16, st);

@@ -466,7 +466,9 @@ hipError_t launch_conv_bf16(const ConvArgs &a, int tile, const Sink &sk) {
     if (tile == TILE_STEM) return launch_conv_stem(a, sk);
     return conv_common(a, tile, 2, "conv_bf16", true, sk);
 }
-hipError_t launch_conv_f32(const ConvArgs &a, const Sink &sk) { return conv_common(a, -1, 4, "conv_f32", false, sk); }
+hipError_t launch_conv_f32(const ConvArgs &a, const Sink &sk) {
+    return conv_common(a, -1, 4, "conv_f32", !a.direct, sk);
+}
 
 // The static scratch: one host block registered as a live allocation
 // (not counted as an allocation of the library).
@@ -505,7 +507,8 @@ hipError_t launch_conv_reduce(const ReduceArgs &a, bool bf16, const Sink &sk) {
 
 // reads_w: the GEMV pass (reads weights and inputs; writes the partial
 // sums when split, else the outputs); otherwise the split-K reduction.
-static hipError_t fc_common(const FcArgs &a, int esz, const char *kern, bool reads_w, const Sink &sk) {
+static hipError_t fc_common(const FcArgs &a, const char *kern, bool reads_w, const Sink &sk) {
+    constexpr int esz = 2;
     ++launches;
     begin_node(sk, kern);
     bool ok = a.M > 0 && a.N > 0 && a.N % 8 == 0 && a.K % 8 == 0 && a.nseg >= 1 && a.seg[0].f_start == 0;
@@ -517,8 +520,7 @@ static hipError_t fc_common(const FcArgs &a, int esz, const char *kern, bool rea
     }
     const bool split = a.k_splits > 1;
     const bool writes_out = !reads_w || !split || a.counters;
-    if (a.grouped && esz != 2) ok = false;
-    if (reads_w && esz == 2 && split && a.counters)
+    if (reads_w && split && a.counters)
         ok &= chk(a.counters, (long long)(a.N + 63) / 64 * (a.grouped ? a.nseg : 1) * 4, "counters", kern, true);
     if (reads_w && !a.grouped) ok &= chk(a.w, (long long)a.N * a.K * esz, "weights", kern);
     for (int i = 0; reads_w && a.grouped && i < a.nseg; ++i)
@@ -537,11 +539,21 @@ static hipError_t fc_common(const FcArgs &a, int esz, const char *kern, bool rea
     if (split && reads_w && a.counters) ok &= chk(a.counters, (long long)(a.N + 63) / 64 * 4, "counters", kern, true);
     return verdict(ok);
 }
-hipError_t launch_fc_bf16(const FcArgs &a, const Sink &sk) { return fc_common(a, 2, "fc_bf16", true, sk); }
-hipError_t launch_fc_f32(const FcArgs &a, const Sink &sk) { return fc_common(a, 4, "fc_f32", true, sk); }
-hipError_t launch_fc_reduce(const FcArgs &a, bool bf16, const Sink &sk) {
-    return fc_common(a, bf16 ? 2 : 4, "fc_reduce", false, sk);
+hipError_t launch_fc_bf16(const FcArgs &a, const Sink &sk) {
+    // the largest grid slice's frames and depth fit the kernel's LDS
+    int frames = a.grouped ? 0 : a.M;
+    for (int i = 0; a.grouped && i < a.nseg; ++i)
+        frames = std::max(frames, (i + 1 < a.nseg ? a.seg[i + 1].f_start : a.M) - a.seg[i].f_start);
+    if (frames < 1 || frames > 64 || (a.k_splits > 1 && a.k_per_split % 128) ||
+        fc_slice_elems(frames, std::min(a.K, a.k_per_split)) > FC_X_ELEMS) {
+        ++violations;
+        last = "fc_bf16: input slice beyond the kernel's LDS";
+        std::fprintf(stderr, "hoststub violation: %s\n", last.c_str());
+        return hipErrorInvalidValue;
+    }
+    return fc_common(a, "fc_bf16", true, sk);
 }
+hipError_t launch_fc_reduce(const FcArgs &a, const Sink &sk) { return fc_common(a, "fc_reduce", false, sk); }
 
 static hipError_t ew(const EwArgs &a, const char *kern, long long in0, long long in1, long long out,
                      int in_esz, int out_esz, const Sink &sk) {
