@@ -456,9 +456,11 @@ enum {
                                     waves, 256x64 and 64x256 of 4) with
                                     split-K still chosen. A forced tile a
                                     conv cannot use falls back to 64x64    */
-    GEMEL_OPT_CONV_SPLITS = 8,   /* 0 (default): split-K chosen per conv;
-                                    n >= 1: force n depth splits (capped
-                                    so that every split has work)          */
+    GEMEL_OPT_CONV_SPLITS = 8,   /* bf16 convs: 0 (default): split-K chosen
+                                    per conv; n >= 1: force n depth splits
+                                    (capped so that every split has work).
+                                    float32 sums have one order, whatever
+                                    the round                              */
     GEMEL_OPT_STREAMS = 9,       /* 1..8 (default 3): at most this many
                                     streams carry a round (forked from and
                                     joined to the caller's stream; 1 with
@@ -573,7 +575,12 @@ enum {
                                     two segments), where the LDS-DMA kernel
                                     can take it and the weights are resident.
                                     Results are those of separate launches
-                                    of the same tile configuration. 0: one
+                                    of the same tile configuration. The same
+                                    pooling, upsample or concat layer of
+                                    several models behind one launch, and
+                                    their outputs of one shape that a
+                                    separate launch writes, share a launch
+                                    too (bf16 and float32, same bits). 0: one
                                     launch per model                       */
     GEMEL_OPT_SWAP_CACHE = 20,   /* with a weight budget: 1 = time-shared
                                     rounds over subsets of the models keep
@@ -626,7 +633,7 @@ gemel_status gemel_set_option(gemel_ctx *ctx, int32_t key, int64_t value);
 /* Kernel families reported by gemel_profile. */
 enum {
     GEMEL_K_CONV_MFMA = 0,   /* bf16 implicit-GEMM convolution (MFMA)       */
-    GEMEL_K_CONV_F32 = 1,    /* fp32 direct convolution                     */
+    GEMEL_K_CONV_F32 = 1,    /* fp32 convolution                            */
     GEMEL_K_SPLITK_REDUCE = 2, /* split-K reduction + epilogue (conv, FC)   */
     GEMEL_K_FC = 3,          /* weight-streaming fully connected            */
     GEMEL_K_PACK = 4,        /* NCHW f32 frames -> NHWC                     */

@@ -58,12 +58,14 @@ enum ConvTile {
     TILE_DMA_256x128 = 10, // 4 waves, 128x64 per wave
     TILE_DMA_128x128 = 11, // 4 waves, 64x64 per wave
     TILE_DMA_128x64 = 12,  // 2 waves, 64x64 per wave
-    // 8-channel inputs (k_stem.hip): 128 pixels x 64 channels (256 x 32
-    // when N <= 32), no LDS
+    // 8-channel inputs (k_stem.hip): 128 pixels x 64 channels (256 x 64 in
+    // large 7x7 launches, 256 x 32 when N <= 32), the weights of 64-channel
+    // tiles in LDS
     TILE_STEM = 13,
     // LDS-DMA pipeline with depth steps of 64 (each row load a whole
     // 128-byte line), Cin a multiple of 64
-    TILE_DMA64_256x256 = 14, // 8 waves, 2 stages
+    TILE_DMA64_256x256 = 14, // 8 waves, 2 stages; 224 rows where they leave
+                             // the CUs' last turn less empty (launch_conv_dma)
     TILE_DMA64_256x128 = 15, // 4 waves, 3 stages
     TILE_DMA64_128x128 = 16, // 4 waves, 2 stages
     TILE_DMA64_128x64 = 17,  // 2 waves, 3 stages

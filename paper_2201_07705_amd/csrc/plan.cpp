@@ -474,7 +474,9 @@ bool direct_output(const Layer &l) {
 // the ResNet, VGG and Darknet workloads): tiles run in waves of (256 CUs x
 // resident tiles per CU); a wave costs its tiles' FLOPs at the tile shape's
 // MFMA efficiency plus a per-wave latency; split-K adds the partial-sum
-// round trip through memory.
+// round trip through memory. (The depth-64 256x256 tile is estimated with its
+// 256 rows, also where the launcher takes 224; the timed choice among the best
+// estimates runs what the launcher takes.)
 struct TileCost {
     int tile;
     double eff;   // MFMA efficiency of the tile shape
